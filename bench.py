@@ -44,8 +44,8 @@ TOL = 1e-5
 # + 32 TCC_EA0_RDREQ_32B, write bytes = 64 TCC_EA0_WRREQ_64B + 32 (the rest of
 # TCC_EA0_WRREQ); the 1 GiB device copy this benchmark times reads and writes
 # exactly its size by the same formulas (profiles/traffic_2d_256_radial.md,
-# profiles/traffic_3d_128_koosh.md).  An entry applies only while kernels.hip
-# has the recorded sha256 prefix and the plan uses the recorded options;
+# profiles/traffic_3d_128_koosh.md).  An entry applies only while the kernel
+# sources have the recorded sha256 prefix and the plan uses the recorded options;
 # otherwise traffic is reported as null.
 MEASURED_TRAFFIC: dict = {
     ("k_grid", "2d_256_golden_radial"): {
@@ -61,8 +61,12 @@ MEASURED_TRAFFIC: dict = {
 
 
 def kernels_hash() -> str:
-    with open(os.path.join(ROOT, "paper_1710_03197_amd", "csrc", "kernels.hip"), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    csrc = os.path.join(ROOT, "paper_1710_03197_amd", "csrc")
+    h = hashlib.sha256()
+    for name in sorted(n for n in os.listdir(csrc) if n.endswith(".hip") or n == "device.h"):
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def prod(v):

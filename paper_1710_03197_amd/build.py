@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnufft_mi355x.so")
-SOURCES = ["kernels.hip", "kb_host.cpp", "api.cpp"]
+SOURCES = ["gather.hip", "gridding.hip", "fft.hip", "points.hip", "kb_host.cpp", "api.cpp"]
+HEADERS = ["device.h", "nufft_internal.h"]
 ARCH = os.environ.get("NUFFT_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [
@@ -55,11 +56,11 @@ def _stale(obj: str, src: str) -> bool:
     """True when obj is missing or older than its source or any header."""
     if not os.path.exists(obj):
         return True
-    deps = [src, os.path.join(CSRC, "nufft_internal.h"), os.path.join(ROOT, "include", "nufft_mi355x.h")]
+    deps = [src, os.path.join(ROOT, "include", "nufft_mi355x.h")] + [os.path.join(CSRC, h) for h in HEADERS]
     return any(os.path.getmtime(d) > os.path.getmtime(obj) for d in deps)
 
 
-def build(verbose: bool = False, jobs: int = 3, incremental: bool = False) -> str:
+def build(verbose: bool = False, jobs: int = 6, incremental: bool = False) -> str:
     """Compile every source (incremental=True: only those whose object is
     older than the source or a header) and link the library."""
     objdir = os.path.join(HERE, "_build")

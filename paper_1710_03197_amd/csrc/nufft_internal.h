@@ -80,7 +80,7 @@ std::vector<float2> twiddles(int K);
 // 8, 2, 3, 5; 2: 3, 5, 8, 4, 2; 3: schedule 0 with its passes reversed.
 bool radix_plan(int K, RadixPlan *rp, int schedule = 0);
 
-// ---- device kernel launchers (kernels.hip).  All asynchronous on `s`.
+// ---- device kernel launchers (the .hip files).  All asynchronous on `s`.
 
 // Forward pass along the contiguous last axis: pad N -> K, scaling, coil
 // multiply; x [B][rows][N] -> out [B*C][rows][K].
