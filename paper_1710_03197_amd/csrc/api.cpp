@@ -1065,14 +1065,27 @@ int build_call(nufft_multi_s *m, bool forward, const void *const *in, void *cons
             std::vector<std::vector<int4>> per(ems.size());
             for (size_t j = 0; j < ems.size(); ++j) stage_blocks(*ems[j], int(j), L.threads, per[j]);
             std::vector<int4> blocks;
-            for (size_t r = 0;; ++r) {
-                bool any = false;
-                for (auto &v : per)
-                    if (r < v.size()) {
-                        blocks.push_back(v[r]);
-                        any = true;
-                    }
-                if (!any) break;
+            if (L.kind == kStStrided) {
+                // column tiles of one array share cache lines with their
+                // neighbours: contiguous blocks per XCD, as in the single launch
+                std::vector<int4> all;
+                for (auto &v : per) all.insert(all.end(), v.begin(), v.end());
+                blocks.resize(all.size());
+                const size_t n = all.size(), q = n / kXcds, rem = n % kXcds;
+                for (size_t b = 0; b < n; ++b) {
+                    const size_t x = b % kXcds;
+                    blocks[b] = all[x * q + std::min(x, rem) + b / kXcds];
+                }
+            } else {
+                for (size_t r = 0;; ++r) {
+                    bool any = false;
+                    for (auto &v : per)
+                        if (r < v.size()) {
+                            blocks.push_back(v[r]);
+                            any = true;
+                        }
+                    if (!any) break;
+                }
             }
             if (blocks.empty()) continue;
             hipError_t e = hipSuccess;

@@ -384,6 +384,20 @@ __global__ __launch_bounds__(THREADS) void k_first_pass_multi(const FirstJob *__
     first_pass_body<THREADS>(j.a, j.lpw, b.y);
 }
 
+// Logical block of workgroup b when consecutive blocks should share an XCD:
+// the hardware deals workgroups round-robin over the 8 XCDs, so XCD x takes
+// the x-th contiguous eighth of the blocks.  Neighbouring column tiles then
+// meet in one L2: a tile's rows are W * 8 bytes (24 to 64), so the 128-byte
+// lines they share are fetched and written back once instead of by several
+// XCDs.  Measured, dealt round-robin -> contiguous: 8 grids of 640 x 640 (48-
+// byte rows) forward 28.3 -> 22.8 us, inverse 38.0 -> 29.5; 240 x 240 x 192,
+// two passes each, 82.6 -> 74.2 and 102.7 -> 88.4 us; 256^3 (128-byte rows)
+// unchanged at 78 and 86 us.
+__device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned n) {
+    const unsigned x = b % kXcds, q = n / kXcds, r = n % kXcds;
+    return x * q + min(x, r) + b / kXcds;
+}
+
 // SPLIT (inverse only): the first inverse pass of an adjoint whose split
 // gridding tiles are still partial tiles (its own instantiation, so the
 // common passes keep their register budget).
@@ -534,7 +548,7 @@ __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int 
 
 template <int THREADS, bool INV, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void k_strided_pass(StridedPassArgs a, int W, int64_t ntc) {
-    strided_pass_body<THREADS, INV, SPLIT>(a, W, ntc, blockIdx.x);
+    strided_pass_body<THREADS, INV, SPLIT>(a, W, ntc, xcd_block(blockIdx.x, gridDim.x));
 }
 
 template <int THREADS, bool INV, bool SPLIT>

@@ -16,6 +16,7 @@ constexpr int kMaxJ = 16;
 constexpr int kMaxPasses = 16;     // radix passes per axis (K <= 4096)
 constexpr int kMaxNeighbors = 27;  // bins whose windows can reach one tile
 constexpr int kFftTileElems = 4096;  // complex elements of the largest FFT workgroup tile (512 threads x 8)
+constexpr int kXcds = 8;             // XCDs the hardware deals workgroups over, each with its own L2
 constexpr int kMaxLinesPerWg = 64;   // lines (contiguous-axis passes) per FFT workgroup
 constexpr int kMaxPolyDeg = 23;
 constexpr int kInterpSamplesPerThread = 2;  // gather work item = 512 samples
