@@ -121,9 +121,10 @@ int nufft_plan(int d, const int64_t *N, const int64_t *K, int J, int64_t M,
  *                 only (with min-max: NUFFT_ERR_UNSUPPORTED); 0: evaluate on
  *                 the fly
  *   fft_radix     radix schedule of the Stockham FFT passes on every axis
- *                 (Section 2.1 "Oversampled FFT"): 0: radices 8, 4, 2, 3, 5
- *                 taken greedily in that order; 1: 4, 8, 2, 3, 5; 2: 3, 5,
- *                 8, 4, 2; 3: schedule 0's passes in reverse order
+ *                 (Section 2.1 "Oversampled FFT"): 0: the fewest passes over
+ *                 radices 2 to 6 and 8; 1: radices 4, 8, 2, 3, 5
+ *                 taken greedily in that order; 2: 3, 5, 8, 4, 2; 3: 8, 4, 2,
+ *                 3, 5, the passes then reversed
  *   grid_waves    wavefronts per work item of the gridding by 4 x 4 blocks:
  *                 4 (the default, 0 asks for it) sum their partial tiles
  *                 in a fixed order at the end; 1: one wavefront per item,

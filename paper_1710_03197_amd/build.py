@@ -28,6 +28,11 @@ FLAGS = [
 ]
 
 
+# per file, after FLAGS: FFT passes that differ only in what they load must give
+# the same bits, so products fuse as the source writes them in every instance
+FILE_FLAGS = {"fft.hip": ["-ffp-contract=on"]}
+
+
 def hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc"):
         if cand and os.path.exists(cand):
@@ -72,7 +77,7 @@ def build(verbose: bool = False, jobs: int = 6, incremental: bool = False) -> st
         objs.append(obj)
         if incremental and not _stale(obj, os.path.join(CSRC, src)):
             continue
-        cmd = [hipcc(), *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc(), *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd)))

@@ -862,7 +862,7 @@ constexpr int kMultiCache = 4;  // pointer sets kept per direction
 struct MultiLaunch {
     int kind = 0;
     int threads = 0;
-    bool inverse = false, split = false, staged = false;
+    bool inverse = false, split = false, staged = false, coils = false;
     GridArgs proto{};  // gridding: the kernel instance
     int J = 0, d = 0;
     size_t lds = 0;
@@ -995,15 +995,16 @@ void stage_blocks(const Emitted &em, int job, int threads, std::vector<int4> &ou
 // Key of the kernel instance a recorded launch uses (launches with equal keys
 // in one slot share a multi-problem launch).  FFT passes share one
 // workgroup size per slot (the largest any problem needs), so only the
-// strided pass's direction and split-tile form separate them.
+// strided pass's direction and split-tile form and
+// the last pass's coils separate them.
 int64_t stage_key(const Emitted &em) {
     switch (em.kind) {
-        case kStFirst: return 0;
+        case kStFirst: return em.first.coils ? 1 : 0;
         case kStStrided: {
             const bool split = em.strided.inverse && em.strided.split_of_tile != nullptr;
             return (em.strided.inverse ? 2 : 0) + (split ? 1 : 0);
         }
-        case kStLast: return 0;
+        case kStLast: return (last_pass_coils(em.last) ? 1 : 0);
         case kStInterp: return em.interp.items ? 1 : 0;
         case kStGrid: return grid_variant(em.grid);
         default: return 0;
@@ -1095,6 +1096,7 @@ int build_call(nufft_multi_s *m, bool forward, const void *const *in, void *cons
                     for (const Emitted *em : ems) {
                         const FftLaunch fl = first_pass_launch(em->first, L.threads);
                         jobs.push_back(FirstJob{em->first, fl.p0});
+                        L.coils = em->first.coils != nullptr;
                         L.lds = std::max(L.lds, fl.lds);
                     }
                     e = upload_jobs(jobs, &L.jobs);
@@ -1117,6 +1119,7 @@ int build_call(nufft_multi_s *m, bool forward, const void *const *in, void *cons
                     for (const Emitted *em : ems) {
                         const FftLaunch fl = last_pass_launch(em->last, L.threads);
                         jobs.push_back(LastJob{em->last, fl.p0, int(fl.p1)});
+                        L.coils = last_pass_coils(em->last);
                         L.lds = std::max(L.lds, fl.lds);
                     }
                     e = upload_jobs(jobs, &L.jobs);
@@ -1171,13 +1174,13 @@ hipError_t issue(const MultiLaunch &L, hipStream_t s) {
     switch (L.kind) {
         case kStFirst:
             return launch_first_pass_multi(static_cast<const FirstJob *>(L.jobs), L.blocks, L.nblocks, L.threads,
-                                           L.lds, s);
+                                           L.coils, L.lds, s);
         case kStStrided:
             return launch_strided_pass_multi(static_cast<const StridedJob *>(L.jobs), L.blocks, L.nblocks, L.threads,
                                              L.inverse, L.split, L.lds, s);
         case kStLast:
-            return launch_last_pass_multi(static_cast<const LastJob *>(L.jobs), L.blocks, L.nblocks, L.threads, L.lds,
-                                          s);
+            return launch_last_pass_multi(static_cast<const LastJob *>(L.jobs), L.blocks, L.nblocks, L.threads,
+                                          L.coils, L.lds, s);
         case kStInterp:
             return launch_interp_multi(static_cast<const InterpArgs *>(L.jobs), L.blocks, L.nblocks, L.J, L.d,
                                        L.staged, L.lds, s);
@@ -1546,7 +1549,7 @@ int nufft_plan_ex(int d, const int64_t *N, const int64_t *K, int J, int64_t M, c
         if ((e = upload(&p->scale[a], p->minmax ? minmax_scaling(int(N[a]), int(K[a]), J, beta)
                                                 : kb_scaling(int(N[a]), int(K[a]), J, beta))) != hipSuccess ||
             (p->minmax && (e = upload(&p->phase[a], half_phase(int(K[a])))) != hipSuccess) ||
-            (e = upload(&p->tw[a], twiddles(int(K[a])))) != hipSuccess ||
+            (e = upload(&p->tw[a], pass_twiddles(int(K[a]), p->rp[a]))) != hipSuccess ||
             (e = upload(&p->coef[a], coef_rows(p->ker[a].coef, J, p->ker[a].deg, coef_row_width(J), &p->nq[a]))) !=
                 hipSuccess ||
             (e = upload(&p->dcoef[a], coef_rows(p->ker[a].dcoef, J, p->ker[a].deg_d, coef_row_width(J),
@@ -1937,7 +1940,7 @@ int nufft_toeplitz_plan(nufft_plan_t plan, const float *w_dev, void *stream, nuf
         std::vector<float> ones(size_t(plan->N[a]), 1.0f);
         std::vector<float> inv(size_t(N2[a]), float(1.0 / double(N2[a])));
         hipError_t e;
-        if ((e = upload(&t->tw[a], twiddles(int(N2[a])))) != hipSuccess ||
+        if ((e = upload(&t->tw[a], pass_twiddles(int(N2[a]), t->rp[a]))) != hipSuccess ||
             (e = upload(&t->ones[a], ones)) != hipSuccess || (e = upload(&t->inv[a], inv)) != hipSuccess) {
             destroy_toeplitz(t.get());
             return hip_fail(e, "upload Toeplitz constants");

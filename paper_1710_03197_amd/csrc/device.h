@@ -47,7 +47,8 @@ struct FastDiv {
     unsigned m;
     int d;
     __device__ __forceinline__ FastDiv() : m(0u), d(1) {}
-    __device__ __forceinline__ explicit FastDiv(int D) : m(D > 1 ? 0xFFFFFFFFu / unsigned(D) + 1u : 0u), d(D) {}
+    __device__ __forceinline__ explicit FastDiv(int D)  // D uniform: one scalar register
+        : m(__builtin_amdgcn_readfirstlane(D > 1 ? 0xFFFFFFFFu / unsigned(D) + 1u : 0u)), d(D) {}
     __device__ __forceinline__ FastDiv(unsigned magic, int D) : m(magic), d(D) {}  // magic made on the host
     __device__ __forceinline__ int div(int e) const { return d > 1 ? int(__umulhi(unsigned(e), m)) : e; }
     __device__ __forceinline__ int rem(int e, int q) const { return e - __umul24(q, d); }

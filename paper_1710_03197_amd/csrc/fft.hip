@@ -7,6 +7,8 @@
 //   k_last_pass    inverse FFT along the last axis + crop + S^H + coil combine
 //                  (Section 2.2, multi-coil: sum_i conj(c_i) A^H y_i).
 // All arithmetic is float32.
+#include <type_traits>
+
 #include "device.h"
 
 namespace nufft {
@@ -82,200 +84,322 @@ __device__ __forceinline__ void dft<8>(float2 *v) {
     v[7] = csub(e[3], o3);
 }
 
-// ------------------------------------------------------------ Stockham passes in LDS
-// Element (line, q) of a tile lives at s[line * LS + q * ES].  STRIDED tiles
-// keep lines adjacent (ES = number of lines) so a wavefront's lanes walk
-// across lines; contiguous tiles keep each line contiguous (ES = 1).  A tile
-// holds at most THREADS * kEPT complex elements; a thread handles up to
-// ceil(kEPT / R) butterflies of radix R per pass.  Twiddles e^{-2 pi i e / K}
-// are staged in LDS (tw) once per workgroup.
+// Composite radices R = A B: A-point DFTs over n1 of n = B n1 + n2, the factors
+// e^{-2 pi i n2 k1 / R}, B-point DFTs over n2; X[k1 + A k2].
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<I + 1, N>(f);
+    }
+}
+
+// cos and sin of 2 pi e / R by their Taylor series (argument in (-pi, pi]),
+// evaluated in float64 by the compiler
+constexpr double turn_angle(int e, int R) {
+    return 6.283185307179586476925 * double(2 * e > R ? e - R : e) / double(R);
+}
+constexpr double turn_cos(int e, int R) {
+    const double x = turn_angle(e, R);
+    double t = 1.0, s = 1.0;
+    for (int k = 1; k < 24; ++k) {
+        t *= -x * x / double((2 * k - 1) * (2 * k));
+        s += t;
+    }
+    return s;
+}
+constexpr double turn_sin(int e, int R) {
+    const double x = turn_angle(e, R);
+    double t = x, s = x;
+    for (int k = 1; k < 24; ++k) {
+        t *= -x * x / double((2 * k) * (2 * k + 1));
+        s += t;
+    }
+    return s;
+}
+
+template <int A, int B>
+__device__ __forceinline__ void dft_composite(float2 *v) {
+    constexpr int R = A * B;
+    float2 y[B][A];
+    static_for<0, B>([&](auto n2) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) y[n2][n1] = v[B * n1 + n2];
+        dft<A>(y[n2]);
+        static_for<0, A>([&](auto k1) __attribute__((always_inline)) {
+            constexpr int e = (int(n2) * int(k1)) % R;
+            if constexpr (e != 0) {
+                constexpr float c = float(turn_cos(e, R)), sn = float(turn_sin(e, R));
+                const float2 t = y[n2][k1];
+                if constexpr (4 * e == R)
+                    y[n2][k1] = mul_negi(t);
+                else
+                    y[n2][k1] = make_float2(t.x * c + t.y * sn, t.y * c - t.x * sn);
+            }
+        });
+    });
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+        float2 z[B];
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) z[n2] = y[n2][k1];
+        dft<B>(z);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = z[k2];
+    }
+}
+template <>
+__device__ __forceinline__ void dft<1>(float2 *) {}
+template <>
+__device__ __forceinline__ void dft<6>(float2 *v) { dft_composite<3, 2>(v); }
+
+// ------------------------------------------------------------ Stockham passes
+// A workgroup transforms a tile of whole lines.  The first radix pass reads its
+// elements straight from global memory into registers, the last one stores its
+// results straight from registers; only the exchanges between passes go
+// through LDS, so a line of n passes makes n - 1 trips through it.
+//
+// Element e of line l sits at lds_row(e) * ES + l * LS: STRIDED tiles keep
+// lines adjacent (ES = number of lines, LS = 1) so a wavefront's lanes walk
+// across lines; contiguous tiles keep each line contiguous (ES = 1, LS =
+// lds_row(K)).  The spare element after every 8 keeps the radix-8 writes (8
+// apart in consecutive lanes) off one another's banks.
+//
+// What bounds the passes: at few workgroups (2D, one image) the chain of memory
+// round trip, exchanges and barriers; otherwise memory.  Measured against
+// staging every element through LDS on the way in and out (n + 1 trips, 2 n + 1
+// barriers, twiddles picked from one table with bank conflicts): 256^3 two
+// strided passes 78 -> 65 us forward and 86 -> 69 inverse (4.6 and 4.4 TB/s);
+// 240 x 240 x 192 74 -> 52 forward; 24 spirals x 8 coils 1668 -> 910 us over the
+// eight FFT launches.  Radices 9, 10, 12 and 16 (fewer passes for 160, 256 or
+// 640) were tried with 8 and with 16 elements per thread: 130 to 250 registers
+// and 2 to 3 wavefronts per SIMD, 256^3 forward 65 -> 111 us.
+//
+// A tile holds at most kEPT elements per thread; a thread handles up to
+// ceil(kEPT / R) butterflies of radix R per pass.  The workgroup size is read at
+// run time (64 to 512), so each kernel is one instance.  The twiddles of the passes
+// after the first sit in LDS in the order they are read (pass p: [R - 1][Ns]).
+// The inverse transform runs the same passes on values with real and imaginary
+// parts swapped on load and store.
+#define NUFFT_INLINE __attribute__((always_inline))  // on lambdas: their arrays must stay in registers
+
 constexpr int kEPT = 8;  // complex elements per thread
 
-// KC > 0: the line length KC and sub-transform length NSC of this pass are
-// compile-time constants (the common grid sizes), so its index arithmetic
-// folds; the same operations in the same order as the run-time form.
-template <int THREADS, int R, bool INV, bool STRIDED, int KC = 0, int NSC = 0>
-__device__ __forceinline__ void radix_pass(float2 *s, int nlines, int K_, int LS, int ES, int Ns_, int span_,
-                                           unsigned m_ns, unsigned m_nbl, const float2 *tw) {
-    constexpr int NB = (kEPT + R - 1) / R;
-    const int K = KC > 0 ? KC : K_;
-    const int Ns = KC > 0 ? NSC : Ns_;
-    const int span = KC > 0 ? KC / ((NSC > 0 ? NSC : 1) * R) : span_;
-    const int nbl = K / R;
-    const int total = nlines * nbl;
-    // (the line count's magic is made per pass: kept across passes it costs
-    // the strided passes about 20 registers)
-    const FastDiv by_line = STRIDED ? FastDiv(nlines) : FastDiv(m_nbl, nbl), by_ns(m_ns, Ns);
-    float2 v[NB][R];
-    int lidx[NB], jidx[NB];
-#pragma unroll
-    for (int it = 0; it < NB; ++it) {
-        const int b = threadIdx.x + it * THREADS;
-        lidx[it] = 0;
-        jidx[it] = 0;
-        if (b < total) {
-            int line, j;
-            if (STRIDED) {
-                j = by_line.div(b);
-                line = by_line.rem(b, j);
-            } else if constexpr (KC > 0) {
-                line = b / (KC / R);
-                j = b - line * (KC / R);
-            } else {
-                line = by_line.div(b);
-                j = by_line.rem(b, line);
-            }
-            lidx[it] = line;
-            jidx[it] = j;
-            const float2 *p = s + line * LS + j * ES;
-#pragma unroll
-            for (int r = 0; r < R; ++r) v[it][r] = p[r * nbl * ES];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < NB; ++it) {
-        const int b = threadIdx.x + it * THREADS;
-        if (b < total) {
-            const int j = jidx[it];
-            int jq, k;
-            if constexpr (KC > 0) {
-                jq = j / NSC;
-                k = j - jq * NSC;
-            } else {
-                jq = by_ns.div(j);
-                k = by_ns.rem(j, jq);
-            }
-            const int step = __umul24(k, span);
-#pragma unroll
-            for (int r = 1; r < R; ++r) {
-                float2 w = tw[r * step];
-                if (INV) w.y = -w.y;
-                v[it][r] = cmul(v[it][r], w);
-            }
-            if (INV) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) v[it][r].y = -v[it][r].y;
-            }
-            dft<R>(v[it]);
-            if (INV) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) v[it][r].y = -v[it][r].y;
-            }
-            const int idxD = __umul24(jq, Ns * R) + k;
-            float2 *q = s + lidx[it] * LS + idxD * ES;
-#pragma unroll
-            for (int r = 0; r < R; ++r) q[r * Ns * ES] = v[it][r];
-        }
-    }
-    __syncthreads();
-}
+__host__ __device__ __forceinline__ constexpr int lds_row(int e) { return e + (e >> 3); }
+__device__ __forceinline__ float2 swap_if(bool c, float2 v) { return c ? make_float2(v.y, v.x) : v; }
 
-template <int THREADS, bool INV, bool STRIDED>
-__device__ void lds_fft(float2 *s, int nlines, int K, int LS, int ES, const RadixPlan &rp, const float2 *tw) {
-    // the grid sizes of the common workloads (and their Toeplitz 2N grids)
-    // with their radix plans spelled out at compile time
-    if (K == 512 && rp.n == 3 && rp.r[0] == 8 && rp.r[1] == 8 && rp.r[2] == 8) {
-        radix_pass<THREADS, 8, INV, STRIDED, 512, 1>(s, nlines, K, LS, ES, 1, 0, 0u, 0u, tw);
-        radix_pass<THREADS, 8, INV, STRIDED, 512, 8>(s, nlines, K, LS, ES, 8, 0, 0u, 0u, tw);
-        radix_pass<THREADS, 8, INV, STRIDED, 512, 64>(s, nlines, K, LS, ES, 64, 0, 0u, 0u, tw);
-        return;
-    }
-    if (K == 256 && rp.n == 3 && rp.r[0] == 8 && rp.r[1] == 8 && rp.r[2] == 4) {
-        radix_pass<THREADS, 8, INV, STRIDED, 256, 1>(s, nlines, K, LS, ES, 1, 0, 0u, 0u, tw);
-        radix_pass<THREADS, 8, INV, STRIDED, 256, 8>(s, nlines, K, LS, ES, 8, 0, 0u, 0u, tw);
-        radix_pass<THREADS, 4, INV, STRIDED, 256, 64>(s, nlines, K, LS, ES, 64, 0, 0u, 0u, tw);
-        return;
-    }
-    int Ns = 1;
-    for (int p = 0; p < rp.n; ++p) {
-        const int R = rp.r[p];
-        const int sp = rp.span[p];
-        const unsigned mn = rp.m_ns[p], mb = rp.m_nbl[p];
-        switch (R) {
-            case 8: radix_pass<THREADS, 8, INV, STRIDED>(s, nlines, K, LS, ES, Ns, sp, mn, mb, tw); break;
-            case 4: radix_pass<THREADS, 4, INV, STRIDED>(s, nlines, K, LS, ES, Ns, sp, mn, mb, tw); break;
-            case 2: radix_pass<THREADS, 2, INV, STRIDED>(s, nlines, K, LS, ES, Ns, sp, mn, mb, tw); break;
-            case 3: radix_pass<THREADS, 3, INV, STRIDED>(s, nlines, K, LS, ES, Ns, sp, mn, mb, tw); break;
-            case 5: radix_pass<THREADS, 5, INV, STRIDED>(s, nlines, K, LS, ES, Ns, sp, mn, mb, tw); break;
-            default: break;
-        }
-        Ns *= R;
+template <int R>
+constexpr int butterflies() { return (kEPT + R - 1) / R; }
+
+// Line and position of butterfly b of a pass with nbl butterflies per line.
+template <bool STRIDED>
+__device__ __forceinline__ void butterfly_place(int b, int nlines, int nbl, unsigned m_nbl, int &line, int &j) {
+    if constexpr (STRIDED) {
+        const FastDiv by_line(nlines);
+        j = by_line.div(b);
+        line = by_line.rem(b, j);
+    } else {
+        const FastDiv by_nbl(m_nbl, nbl);
+        line = by_nbl.div(b);
+        j = by_nbl.rem(b, line);
     }
 }
 
-// Twiddles into LDS.  A workgroup's tile holds at least one whole line, so a
-// thread stages at most kEPT of the K twiddles; every load is issued before
-// the first LDS write, so the staging costs one memory round trip.
-template <int THREADS>
+// Run f(std::integral_constant<int, R>) for the radix of pass p.
+template <class F>
+__device__ __forceinline__ void with_radix(int R, F &&f) {
+    switch (R) {
+        case 8: f(std::integral_constant<int, 8>()); break;
+        case 6: f(std::integral_constant<int, 6>()); break;
+        case 5: f(std::integral_constant<int, 5>()); break;
+        case 4: f(std::integral_constant<int, 4>()); break;
+        case 3: f(std::integral_constant<int, 3>()); break;
+        case 2: f(std::integral_constant<int, 2>()); break;
+        case 1: f(std::integral_constant<int, 1>()); break;
+        default: break;
+    }
+}
+
+// Twiddles of the later passes into LDS: K - r[0] of them.  At most kEPT
+// per thread (a tile holds at least a whole line), they are loaded before the
+// data and stored after its loads, so they cost no memory round trip of their
+// own.
 struct TwiddleStage {
     float2 v[kEPT];
-    __device__ __forceinline__ void load(const float2 *__restrict__ tw, int K) {
+    __device__ __forceinline__ void load(const float2 *__restrict__ tw, int n) {
 #pragma unroll
         for (int u = 0; u < kEPT; ++u) {
-            const int e = threadIdx.x + u * THREADS;
-            if (e < K) v[u] = tw[e];
+            const int e = threadIdx.x + u * blockDim.x;
+            if (e < n) v[u] = tw[e];
         }
     }
-    __device__ __forceinline__ void store(float2 *tw_lds, int K) const {
+    __device__ __forceinline__ void store(float2 *tw_lds, int n) const {
 #pragma unroll
         for (int u = 0; u < kEPT; ++u) {
-            const int e = threadIdx.x + u * THREADS;
-            if (e < K) tw_lds[e] = v[u];
+            const int e = threadIdx.x + u * blockDim.x;
+            if (e < n) tw_lds[e] = v[u];
         }
     }
 };
 
+// p[off] for a uniform p and a lane's offset of less than 2^32 bytes: a scalar
+// base and one 32-bit register per address.
+__device__ __forceinline__ float2 load_at(const float2 *p, unsigned off_bytes) {
+    return *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(p) + off_bytes);
+}
+__device__ __forceinline__ void store_at(float2 *p, unsigned off_bytes, float2 v) {
+    *reinterpret_cast<float2 *>(reinterpret_cast<char *>(p) + off_bytes) = v;
+}
+
+// First pass: ld.load(it, u, r, line, q) issues the load of element q of a
+// line into the loader's registers, ld.value(it, r) combines it; no twiddles
+// (Ns = 1).  `stage` runs between the loads and the LDS writes.
+template <int R, bool STRIDED, class LD, class ST>
+__device__ __forceinline__ void first_radix(float2 *s, int nlines, int LS, int ES, const RadixPlan &rp, LD &&ld,
+                                            ST &&stage) {
+    constexpr int NB = butterflies<R>();
+    const int nbl = rp.nbl[0], total = nlines * nbl;
+    // (radices other than 8 and 4 one butterfly at a time: the registers of
+    // several would set the kernel's)
+    constexpr int kUnroll = R == 8 || R == 4 ? NB : 1;
+#pragma unroll kUnroll
+    for (int it = 0; it < NB; ++it) {
+        const int b = int(threadIdx.x) + it * int(blockDim.x);
+        int line, j;
+        float2 v[R];
+        butterfly_place<STRIDED>(min(b, total - 1), nlines, nbl, rp.m_nbl[0], line, j);  // (clamped: loads in bounds)
+        ld(line, j, nbl, std::integral_constant<int, R>(), v);
+        if (it == 0) stage();
+        dft<R>(v);
+        if (b < total) {
+            float2 *q = s + line * LS;
+            const int e0 = j * R;
+#pragma unroll
+            for (int r = 0; r < R; ++r) q[lds_row(e0 + r) * ES] = v[r];
+        }
+    }
+    __syncthreads();
+}
+
+// One butterfly of pass p from LDS: its values after the DFT and its place.
+template <int R, bool STRIDED>
+__device__ __forceinline__ void radix_values(const float2 *s, int b, int nlines, int LS, int ES, const RadixPlan &rp,
+                                             int p, const float2 *tw, float2 *v, int &line, int &j, int &k) {
+    const int nbl = rp.nbl[p], Ns = rp.ns[p];
+    const FastDiv by_ns(rp.m_ns[p], Ns);
+    butterfly_place<STRIDED>(b, nlines, nbl, rp.m_nbl[p], line, j);
+    const float2 *q = s + line * LS;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = q[lds_row(j + r * nbl) * ES];
+    k = by_ns.rem(j, by_ns.div(j));
+    const float2 *t = tw + rp.tw_off[p] + k;
+#pragma unroll
+    for (int r = 1; r < R; ++r) v[r] = cmul(v[r], t[(r - 1) * Ns]);
+    dft<R>(v);
+}
+
+// A pass from LDS back to LDS.
+template <int R, bool STRIDED>
+__device__ __forceinline__ void middle_radix(float2 *s, int nlines, int LS, int ES, const RadixPlan &rp, int p,
+                                             const float2 *tw) {
+    constexpr int NB = butterflies<R>();
+    const int Ns = rp.ns[p], total = nlines * rp.nbl[p];
+    float2 v[NB][R];
+    int line[NB], e0[NB];
+#pragma unroll
+    for (int it = 0; it < NB; ++it) {
+        int j, k;
+        radix_values<R, STRIDED>(s, min(int(threadIdx.x) + it * int(blockDim.x), total - 1), nlines, LS, ES, rp, p, tw,
+                                 v[it], line[it], j, k);
+        e0[it] = (j - k) * R + k;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < NB; ++it) {
+        if (int(threadIdx.x) + it * int(blockDim.x) < total) {
+            float2 *q = s + line[it] * LS;
+#pragma unroll
+            for (int r = 0; r < R; ++r) q[lds_row(e0[it] + r * Ns) * ES] = v[it][r];
+        }
+    }
+    __syncthreads();
+}
+
+// Last pass: st(line, j, nbl, R, values) stores elements j + r nbl of a line.
+template <int R, bool STRIDED, class ST>
+__device__ __forceinline__ void last_radix(const float2 *s, int nlines, int LS, int ES, const RadixPlan &rp,
+                                           const float2 *tw, ST &&st) {
+    constexpr int NB = butterflies<R>();
+    const int p = rp.n - 1, nbl = rp.nbl[p], total = nlines * nbl;
+    constexpr int kUnroll = R == 8 || R == 4 ? NB : 1;
+#pragma unroll kUnroll
+    for (int it = 0; it < NB; ++it) {
+        const int b = int(threadIdx.x) + it * int(blockDim.x);
+        if (b < total) {
+            float2 v[R];
+            int line, j, k;
+            radix_values<R, STRIDED>(s, b, nlines, LS, ES, rp, p, tw, v, line, j, k);
+            st(line, j, nbl, std::integral_constant<int, R>(), v);
+        }
+    }
+}
+
+// Passes 0 .. upto - 1, from global memory into LDS.
+template <bool STRIDED, class LD, class ST>
+__device__ __forceinline__ void leading_passes(float2 *s, int nlines, int LS, int ES, const RadixPlan &rp, int upto,
+                                               const float2 *tw, LD &&ld, ST &&stage) {
+    with_radix(rp.r[0], [&](auto R) NUFFT_INLINE { first_radix<R, STRIDED>(s, nlines, LS, ES, rp, ld, stage); });
+    for (int p = 1; p < upto; ++p)
+        with_radix(rp.r[p], [&](auto R) NUFFT_INLINE { middle_radix<R, STRIDED>(s, nlines, LS, ES, rp, p, tw); });
+}
 
 // Product of the scaling factors of the leading axes of image row r
 // (row-major over axes 0..d-2), 32-bit index arithmetic.
 __device__ __forceinline__ float row_scale(int d, const int *Nax, const float *const *scale, int r) {
     float sc = 1.0f;
-    for (int a = d - 2; a >= 0; --a) {
-        const int i = r % Nax[a];
-        r /= Nax[a];
-        sc *= scale[a][i];
+#pragma unroll
+    for (int a = kMaxDim - 2; a >= 0; --a) {
+        if (a < d - 1) {
+            int i = r;
+            if (a > 0) {
+                i = r % Nax[a];
+                r /= Nax[a];
+            }
+            sc *= scale[a][i];
+        }
     }
     return sc;
 }
 
-// row_scale with its loads issued at load() and the product formed at value(),
-// so the loads overlap other work.
-struct RowScale {
-    float f[kMaxDim - 1];
-    int n;
-    __device__ __forceinline__ void load(int d, const int *Nax, const float *const *scale, int r) {
-        n = d - 1;
-#pragma unroll
-        for (int a = kMaxDim - 2; a >= 0; --a) {
-            if (a < n) {
-                const int i = r % Nax[a];
-                r /= Nax[a];
-                f[a] = scale[a][i];
-            }
-        }
-    }
-    __device__ __forceinline__ float value() const {
-        float sc = 1.0f;
-#pragma unroll
-        for (int a = kMaxDim - 2; a >= 0; --a)
-            if (a < n) sc *= f[a];
-        return sc;
-    }
-};
-
-// Grid position of image index i on an axis of image size N and grid size K
-// (n = i - N/2 wrapped modulo K), and its inverse (-1 in the zero gap).
-__device__ __forceinline__ int pad_pos(int i, int N, int K) { return i < N / 2 ? K - N / 2 + i : i - N / 2; }
+// Image index of grid position q on an axis of image size N and grid size K
+// (n = i - N/2 wrapped modulo K); -1 in the zero gap.
 __device__ __forceinline__ int src_row(int q, int N, int K) {
     if (q < N / 2) return q + N / 2;
     if (q >= K - N / 2) return q - (K - N / 2);
     return -1;
 }
+// No element of grid positions [q0, q0 + n) lies in the image.
+__device__ __forceinline__ bool dead_rows(int q0, int n, int N, int K) {
+    return q0 >= N / 2 && q0 + n <= K - N / 2;
+}
+__device__ __forceinline__ int grid_row(int i, int N, int K) { return i < N / 2 ? K - N / 2 + i : i - N / 2; }
+
+// n / d and its remainder for uniform n >= 0, d >= 1, by a 32-bit division
+// whenever that is enough.
+__device__ __forceinline__ int64_t divmod(int64_t n, int64_t d, int64_t &rem) {
+    int64_t q;
+    if ((uint64_t(n) | uint64_t(d)) >> 32) {
+        q = n / d;
+    } else {
+        q = int64_t(unsigned(n) / unsigned(d));
+    }
+    rem = n - q * d;
+    return q;
+}
 
 // ------------------------------------------------------------ FFT kernels
 // Dynamic LDS layout of every FFT kernel: [K twiddles][tile].
-template <int THREADS>
+template <bool COILS>
 __device__ __forceinline__ void first_pass_body(const FirstPassArgs &a, int lines_per_wg, int64_t bx) {
     extern __shared__ float2 lds[];
     const int K = a.K, N = a.N;
@@ -284,104 +408,83 @@ __device__ __forceinline__ void first_pass_body(const FirstPassArgs &a, int line
     const int64_t total = int64_t(a.B) * a.C * a.rows;
     const int64_t l0 = bx * lines_per_wg;
     const int nl = int(min(int64_t(lines_per_wg), total - l0));  // 1..64
-    // Line `lane` of the workgroup, known to that lane of every wavefront: the
-    // image and coil row offsets and the product of the leading axes' scaling
-    // factors (applied after the FFT, which is linear along the line).
-    const int lane = threadIdx.x & 63;
-    int xb = 0, cb = 0;
-    RowScale rsf;
-    {
-        const int64_t l = l0 + min(lane, nl - 1);
-        const int g = int(l / a.rows);
-        const int r = int(l - int64_t(g) * a.rows);
-        const int b = g / a.C;
-        const int c = g - b * a.C;
-        rsf.load(a.d, a.Nax, a.scale, r);  // consumed after the FFT
-        xb = (b * int(a.rows) + r) * N;
-        cb = (c * int(a.rows) + r) * N;
-    }
-    TwiddleStage<THREADS> tws;
-    tws.load(a.tw, K);
-    // the tile holds nl * K <= THREADS * kEPT elements: every load is issued
-    // before the first use
-    const int ne = nl * K;
-    const FastDiv byK(K);
+    const int ntw = K - a.rp.r[0];
+    TwiddleStage tws;
+    tws.load(a.tw, ntw);
+    const int rows = int(a.rows);
+    int64_t r0, c0 = 0;
+    const int64_t g0 = divmod(l0, rows, r0);
+    int64_t b0 = g0;
+    if constexpr (COILS) b0 = divmod(g0, a.C, c0);
+    const FastDiv by_rows(rows), by_c(COILS ? a.C : 1);  // (for line numbers < 128, grids < C + 64)
     const float *slast = a.scale[a.d - 1];
-    // (loads land in registers without a default value, so no copy waits for
-    // them; `live` marks the elements that read the image)
-    // (branch-free: indices are clamped into the row and `live` marks the
-    // elements that really read the image, so no load waits on another)
-    float2 xv[kEPT], cv[kEPT];
-    float sv[kEPT];
-    unsigned live = 0;
+    auto load = [&](int lw, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+        constexpr int R = decltype(RC)::value;
+        // line l0 + lw is row r of grid (b, c)
+        int r = int(r0) + lw;
+        const int dg = rows >= kMaxLinesPerWg ? (r >= rows ? 1 : 0) : by_rows.div(r);
+        r -= dg * rows;
+        int64_t b = b0 + dg;
+        int c = 0;
+        if constexpr (COILS) {
+            c = int(c0) + dg;
+            const int db = by_c.div(c);
+            c -= db * a.C;
+            b = b0 + db;
+        }
+        const float2 *x = a.x + (b * rows + r) * N;
+        const float2 *coil = COILS ? a.coils + (int64_t(c) * rows + r) * N : nullptr;
+        // every load first, without branches: zero-gap elements read pixel 0
+        float2 cv[COILS ? R : 1];
+        float sv[R];
 #pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = min(int(threadIdx.x) + u * THREADS, ne - 1);
-        const int lw = byK.div(e);
-        const int i = src_row(byK.rem(e, lw), N, K);
-        live |= (int(threadIdx.x) + u * THREADS < ne && i >= 0) ? 1u << u : 0u;
-        const int ic = max(i, 0);
-        // one grid per image row without coils: line l reads image row l
-        const int xbl = a.C == 1 ? int(l0 + lw) * N : __shfl(xb, lw);
-        xv[u] = a.x[xbl + ic];
-        sv[u] = slast[ic];
-        if (a.coils) cv[u] = a.coils[__shfl(cb, lw) + ic];
-    }
-    // values first, without branches (one wait for all loads), then the writes
+        for (int u = 0; u < R; ++u) {
+            const int i = max(src_row(j + u * nbl, N, K), 0);
+            v[u] = x[i];
+            sv[u] = slast[i];
+            if constexpr (COILS) cv[u] = coil[i];
+        }
+        const float rs = row_scale(a.d, a.Nax, a.scale, r);
 #pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        float2 v = cscale(xv[u], sv[u]);
-        if (a.coils) v = cmul(v, cv[u]);
-        xv[u] = (live & (1u << u)) ? v : make_float2(0.f, 0.f);
-    }
-    tws.store(tw, K);
-#pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = threadIdx.x + u * THREADS;
-        if (e < ne) s[e] = xv[u];
-    }
-    __syncthreads();
-    lds_fft<THREADS, false, false>(s, nl, K, K, 1, a.rp, tw);
-    const float rs = rsf.value();
+        for (int u = 0; u < R; ++u) {
+            const float2 t = cscale(v[u], src_row(j + u * nbl, N, K) >= 0 ? sv[u] * rs : 0.f);
+            if constexpr (COILS)
+                v[u] = cmul(t, cv[u]);
+            else
+                v[u] = t;
+        }
+    };
+    const int LS = lds_row(K);
+    leading_passes<false>(s, nl, LS, 1, a.rp, a.rp.n - 1, tw, load, [&]() NUFFT_INLINE { tws.store(tw, ntw); });
     float2 *out = a.out + l0 * K;
-    float2 pv[kEPT], mv[kEPT];
+    with_radix(a.rp.r[a.rp.n - 1], [&](auto RL) NUFFT_INLINE {
+        last_radix<RL, false>(s, nl, LS, 1, a.rp, tw, [&](int lw, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+            constexpr int R = decltype(RC)::value;
+            float2 *o = out + lw * K + j;
 #pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = min(int(threadIdx.x) + u * THREADS, ne - 1);
-        const int lw = byK.div(e);
-        const int q = byK.rem(e, lw);
-        if (a.phase) pv[u] = a.phase[q];
-        if (a.mult) mv[u] = a.mult[((l0 + lw) % a.rows) * K + q];
-    }
-#pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = min(int(threadIdx.x) + u * THREADS, ne - 1);
-        float2 v = s[e];
-        if (a.d > 1) v = cscale(v, __shfl(rs, byK.div(e)));  // row scale of the element's line
-        if (a.phase) v = cmul(v, pv[u]);
-        if (a.mult) v = cmul(v, mv[u]);
-        pv[u] = v;
-    }
-#pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = threadIdx.x + u * THREADS;
-        if (e < ne) out[e] = pv[u];
-    }
+            for (int u = 0; u < R; ++u) {
+                float2 t = v[u];
+                if (a.phase) t = cmul(t, a.phase[j + u * nbl]);
+                if (a.mult) t = cmul(t, a.mult[((l0 + lw) % a.rows) * K + j + u * nbl]);
+                o[u * nbl] = t;
+            }
+        });
+    });
 }
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_first_pass(FirstPassArgs a, int lines_per_wg) {
-    first_pass_body<THREADS>(a, lines_per_wg, blockIdx.x);
+template <bool COILS>
+__global__ __launch_bounds__(kFftThreads) void k_first_pass(FirstPassArgs a, int lines_per_wg) {
+    first_pass_body<COILS>(a, lines_per_wg, blockIdx.x);
 }
 
 // Many problems in one launch: workgroup b runs block blocks[b].y of problem
 // blocks[b].x, whose arguments sit in jobs[blocks[b].x].
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_first_pass_multi(const FirstJob *__restrict__ jobs,
+template <bool COILS>
+__global__ __launch_bounds__(kFftThreads) void k_first_pass_multi(const FirstJob *__restrict__ jobs,
                                                              const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const FirstJob &j = jobs[b.x];
-    first_pass_body<THREADS>(j.a, j.lpw, b.y);
+    first_pass_body<COILS>(j.a, j.lpw, b.y);
 }
 
 // Logical block of workgroup b when consecutive blocks should share an XCD:
@@ -398,343 +501,299 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned n) {
     return x * q + min(x, r) + b / kXcds;
 }
 
-// SPLIT (inverse only): the first inverse pass of an adjoint whose split
-// gridding tiles are still partial tiles (its own instantiation, so the
-// common passes keep their register budget).
-template <int THREADS, bool INV, bool SPLIT>
+// Forms of the inverse pass with instances of their own, so the plain passes
+// keep their register budget: the first inverse pass of an adjoint whose split
+// gridding tiles are still partial tiles, and the first inverse pass after a
+// Toeplitz product.  A tile's lanes address one slab of K rows by inner columns
+// from scalar row bases; (K / R) rows of it hold less than 2^32 bytes for
+// radices of at least 4, which the first and last radix are wherever a slab
+// reaches 4 GiB (launch_strided_pass checks).
+enum { kPlain, kSplitTiles, kProduct };
+template <bool INV, int FORM>
 __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int W, int64_t ntc, int64_t bid) {
     extern __shared__ float2 lds[];
     const int K = a.K;
     float2 *tw = lds;
     float2 *s = lds + K;
-    const int64_t ct = bid % ntc;
-    const int64_t rest = bid / ntc;
-    const int64_t o = rest % a.outer;
-    const int64_t g = rest / a.outer;
+    int64_t ct, o;
+    const int64_t rest = divmod(bid, ntc, ct);
+    const int64_t g = divmod(rest, a.outer, o);
     const int64_t c0 = ct * W;
     const int wv = int(min(int64_t(W), a.inner - c0));
     const float2 *in = a.in + ((g * a.outer + o) * a.Lin) * a.inner + c0;
     float2 *out = a.out + ((g * a.outer + o) * a.Lout) * a.inner + c0;
-    TwiddleStage<THREADS> tws;
-    tws.load(a.tw, K);
-    // the tile holds K * W <= THREADS * kEPT elements
-    const int ne = K * W;
-    const FastDiv byW(W);
-    // (no default values in the load registers, so no copy waits for a load;
-    // `live` marks the elements that read the input)
-    float2 v[kEPT], mv[kEPT], pv[kEPT];
-    unsigned live = 0;
-    if constexpr (!SPLIT) {
-#pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = threadIdx.x + u * THREADS;
-            const int q = byW.div(min(e, ne - 1));
-            const int w = e - __umul24(q, W);
-            // forward: grid row q takes image row src_row (zero rows when Lin < K,
-            // the centring shift when Lin == K); inverse: the input is the grid
-            const int i = INV ? q : src_row(q, a.Lin, K);
-            if (e < ne && w < wv && i >= 0) {
-                live |= 1u << u;
-                v[u] = in[int64_t(i) * a.inner + w];
-                if (a.mult) mv[u] = a.mult[(o * a.Lin + i) * a.inner + c0 + w];
-                if (INV && a.phase) pv[u] = a.phase[q];
-            }
-        }
-    } else {
-        // First inverse pass of the adjoint: a cell of a split gridding tile is
-        // the sum of its partial tiles in chunk order (the order, hence the bits,
-        // of k_reduce_partials).  Grid row q on axis 0, column c0 + w over the
-        // remaining axes; the input and the cell's split entry are loaded
-        // together, the partial tiles after that.
-        const FastDiv byT0(a.T[0]), byT1(a.T[1]), byT2(a.d > 2 ? a.T[2] : 1), byK2(a.d > 2 ? a.Kax[2] : 1);
-        int2 sp[kEPT];
-        int cellv[kEPT];
-#pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = min(int(threadIdx.x) + u * THREADS, ne - 1);
-            const int q = byW.div(e);
-            const int w = min(e - __umul24(q, W), wv - 1);
-            const int i = INV ? q : max(src_row(q, a.Lin, K), 0);
-            live |= (int(threadIdx.x) + u * THREADS < ne && e - __umul24(q, W) < wv &&
-                     (INV || src_row(q, a.Lin, K) >= 0)) ? 1u << u : 0u;
-            // grid coordinates of the cell: k0 = q, then the column's axes
+    const int ntw = K - a.rp.r[0];
+    const float2 *mul = FORM == kProduct ? a.mult + (o * a.Lin) * a.inner + c0 : nullptr;
+    TwiddleStage tws;
+    tws.load(a.tw, ntw);
+    // forward: grid row q takes image row src_row (zero rows when Lin < K, the
+    // centring shift when Lin == K); inverse: the input is the grid
+    auto load = [&](int w, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+        constexpr int R = decltype(RC)::value;
+        const unsigned off = (unsigned(j) * unsigned(a.inner) + unsigned(w)) * unsigned(sizeof(float2));
+        if constexpr (FORM == kSplitTiles) {
+            // First inverse pass of the adjoint: a cell of a split gridding tile
+            // is the sum of its partial tiles in chunk order (the order, hence
+            // the bits, of k_reduce_partials).  Grid row q on axis 0, column
+            // c0 + w over the remaining axes; the input and the cell's split
+            // entry are loaded together, the partial tiles after that.
+            const FastDiv byT0(a.T[0]), byT1(a.T[1]), byT2(a.d > 2 ? a.T[2] : 1), byK2(a.d > 2 ? a.Kax[2] : 1);
             const int c = int(c0) + w;
             int k1 = c, k2 = 0;
             if (a.d > 2) {
                 k1 = byK2.div(c);
                 k2 = byK2.rem(c, k1);
             }
-            const int t0 = byT0.div(q), t1 = byT1.div(k1);
-            int tile = t0 * a.nt[1] + t1;
-            int cell = byT0.rem(q, t0) * a.T[1] + byT1.rem(k1, t1);
-            if (a.d > 2) {
-                const int t2 = byT2.div(k2);
-                tile = tile * a.nt[2] + t2;
-                cell = cell * a.T[2] + byT2.rem(k2, t2);
-            }
-            v[u] = in[int64_t(i) * a.inner + w];
-            sp[u] = a.split_of_tile[tile];
-            cellv[u] = cell;
-            if (INV && a.phase) pv[u] = a.phase[q];  // (never with a Toeplitz product)
-        }
+            const int t1 = byT1.div(k1), t2 = byT2.div(k2);
+            const int l1 = byT1.rem(k1, t1), l2 = byT2.rem(k2, t2);
+            int2 sp[R];
+            int cell[R];
 #pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int n = sp[u].y;
-            if (n > 0) {
-                const float2 *pp = a.partials + (g * a.n_slots + sp[u].x) * a.tile_cells + cellv[u];
-                // kReduceLanes interleaved sums (chunk c into sum c mod
-                // kReduceLanes, in chunk order), then added in lane order
-                float2 acc[kReduceLanes];
-#pragma unroll
-                for (int j = 0; j < kReduceLanes; ++j) acc[j] = make_float2(0.f, 0.f);
-                for (int k0 = 0; k0 < n; k0 += kReduceLanes) {
-                    float2 t[kReduceLanes];
-#pragma unroll
-                    for (int j = 0; j < kReduceLanes; ++j)
-                        if (k0 + j < n) t[j] = pp[int64_t(k0 + j) * a.tile_cells];
-#pragma unroll
-                    for (int j = 0; j < kReduceLanes; ++j)
-                        if (k0 + j < n) acc[j] = cadd(acc[j], t[j]);
+            for (int u = 0; u < R; ++u) {
+                const int q = j + u * nbl;
+                const int t0 = byT0.div(q);
+                int tile = t0 * a.nt[1] + t1;
+                cell[u] = byT0.rem(q, t0) * a.T[1] + l1;
+                if (a.d > 2) {
+                    tile = tile * a.nt[2] + t2;
+                    cell[u] = cell[u] * a.T[2] + l2;
                 }
+                v[u] = load_at(in + int64_t(u * nbl) * a.inner, off);
+                sp[u] = a.split_of_tile[tile];
+            }
 #pragma unroll
-                for (int j = 1; j < kReduceLanes; ++j) acc[0] = cadd(acc[0], acc[j]);
-                v[u] = acc[0];
+            for (int u = 0; u < R; ++u) {
+                const int n = sp[u].y;
+                if (n > 0) {
+                    const float2 *pp = a.partials + (g * a.n_slots + sp[u].x) * a.tile_cells + cell[u];
+                    // kReduceLanes interleaved sums (chunk c into sum c mod
+                    // kReduceLanes, in chunk order), then added in lane order
+                    float2 acc[kReduceLanes];
+#pragma unroll
+                    for (int i = 0; i < kReduceLanes; ++i) acc[i] = make_float2(0.f, 0.f);
+                    for (int k0 = 0; k0 < n; k0 += kReduceLanes) {
+                        float2 t[kReduceLanes];
+#pragma unroll
+                        for (int i = 0; i < kReduceLanes; ++i)
+                            if (k0 + i < n) t[i] = pp[int64_t(k0 + i) * a.tile_cells];
+#pragma unroll
+                        for (int i = 0; i < kReduceLanes; ++i)
+                            if (k0 + i < n) acc[i] = cadd(acc[i], t[i]);
+                    }
+#pragma unroll
+                    for (int i = 1; i < kReduceLanes; ++i) acc[0] = cadd(acc[0], acc[i]);
+                    v[u] = acc[0];
+                }
+            }
+        } else {
+            float2 mv[FORM == kProduct ? R : 1];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int q0 = u * nbl;
+                if constexpr (INV) {
+                    v[u] = load_at(in + int64_t(q0) * a.inner, off);
+                    if constexpr (FORM == kProduct) mv[u] = load_at(mul + int64_t(q0) * a.inner, off);
+                } else {
+                    // (no branches: zero rows read row 0; cell counts fit 32 bits)
+                    const int i = src_row(j + q0, a.Lin, K);
+                    v[u] = in[unsigned(max(i, 0)) * unsigned(a.inner) + unsigned(w)];
+                }
+            }
+            if constexpr (!INV) {
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (src_row(j + u * nbl, a.Lin, K) < 0) v[u] = make_float2(0.f, 0.f);
+            }
+            if constexpr (FORM == kProduct) {
+#pragma unroll
+                for (int u = 0; u < R; ++u) v[u] = cmul(v[u], mv[u]);
             }
         }
-    }
-    // values first, without branches (one wait for all loads), then the writes
+        if constexpr (INV) {
 #pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        float2 x = v[u];
-        if (!SPLIT && a.mult) x = cmul(x, mv[u]);
-        if (INV && a.phase) x = cmulcj(pv[u], x);
-        v[u] = (live & (1u << u)) ? x : make_float2(0.f, 0.f);
-    }
-    tws.store(tw, K);
-#pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = threadIdx.x + u * THREADS;
-        if (e < ne) s[e] = v[u];
-    }
-    __syncthreads();
-    lds_fft<THREADS, INV, true>(s, W, K, 1, W, a.rp, tw);
-    // Lout * W <= K * W outputs
-    const int no = a.Lout * W;
-    if (!INV && a.phase) {
-#pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = min(int(threadIdx.x) + u * THREADS, no - 1);
-            pv[u] = a.phase[byW.div(e)];
+            for (int u = 0; u < R; ++u) {
+                if (a.phase) v[u] = cmulcj(a.phase[j + u * nbl], v[u]);
+                v[u] = swap_if(true, v[u]);
+            }
         }
-    }
-    // values first, without branches, then the writes
+    };
+    leading_passes<true>(s, wv, 1, wv, a.rp, a.rp.n - 1, tw, load, [&]() NUFFT_INLINE { tws.store(tw, ntw); });
+    with_radix(a.rp.r[a.rp.n - 1], [&](auto RL) NUFFT_INLINE {
+        last_radix<RL, true>(s, wv, 1, wv, a.rp, tw, [&](int w, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+            constexpr int R = decltype(RC)::value;
+            const unsigned off = (unsigned(j) * unsigned(a.inner) + unsigned(w)) * unsigned(sizeof(float2));
 #pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = min(int(threadIdx.x) + u * THREADS, no - 1);
-        const int i = byW.div(e);
-        const int q = INV ? pad_pos(i, a.Lout, K) : i;
-        float2 x = s[__umul24(q, W) + byW.rem(e, i)];
-        if (!INV && a.phase) x = cmul(x, pv[u]);
-        v[u] = x;
-    }
-#pragma unroll
-    for (int u = 0; u < kEPT; ++u) {
-        const int e = threadIdx.x + u * THREADS;
-        const int i = byW.div(min(e, no - 1));
-        const int w = e - __umul24(i, W);
-        if (e < no && w < wv) out[int64_t(i) * a.inner + w] = v[u];
-    }
+            for (int u = 0; u < R; ++u) {
+                const int q0 = u * nbl;
+                float2 t = swap_if(INV, v[u]);
+                if constexpr (!INV) {
+                    if (a.phase) t = cmul(t, a.phase[j + q0]);
+                    store_at(out + int64_t(q0) * a.inner, off, t);
+                } else if (!dead_rows(q0, nbl, a.Lout, K)) {
+                    const int i = src_row(j + q0, a.Lout, K);
+                    if (i >= 0) out[unsigned(i) * unsigned(a.inner) + unsigned(w)] = t;
+                }
+            }
+        });
+    });
 }
 
-template <int THREADS, bool INV, bool SPLIT>
-__global__ __launch_bounds__(THREADS) void k_strided_pass(StridedPassArgs a, int W, int64_t ntc) {
-    strided_pass_body<THREADS, INV, SPLIT>(a, W, ntc, xcd_block(blockIdx.x, gridDim.x));
+template <bool INV, int FORM>
+__global__ __launch_bounds__(kFftThreads) void k_strided_pass(StridedPassArgs a, int W, int64_t ntc) {
+    strided_pass_body<INV, FORM>(a, W, ntc, xcd_block(blockIdx.x, gridDim.x));
 }
 
-template <int THREADS, bool INV, bool SPLIT>
-__global__ __launch_bounds__(THREADS) void k_strided_pass_multi(const StridedJob *__restrict__ jobs,
+template <bool INV, int FORM>
+__global__ __launch_bounds__(kFftThreads) void k_strided_pass_multi(const StridedJob *__restrict__ jobs,
                                                                const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const StridedJob &j = jobs[b.x];
-    strided_pass_body<THREADS, INV, SPLIT>(j.a, j.W, j.ntc, b.y);
+    strided_pass_body<INV, FORM>(j.a, j.W, j.ntc, b.y);
 }
 
-template <int THREADS>
+template <bool COILS>
 __device__ __forceinline__ void last_pass_body(const LastPassArgs &a, int rows_per_wg, int coils_per_round, int64_t bx) {
     extern __shared__ float2 lds[];
-    __shared__ float rsc[kMaxLinesPerWg];
     const int K = a.K, N = a.N, C = a.C;
     float2 *tw = lds;
     float2 *s = lds + K;
     const int64_t nrt = (a.rows + rows_per_wg - 1) / rows_per_wg;
-    const int64_t b = bx / nrt;
-    const int64_t r0 = (bx % nrt) * rows_per_wg;
+    int64_t rt;
+    const int64_t b = divmod(bx, nrt, rt);
+    const int64_t r0 = rt * rows_per_wg;
     const int nr = int(min(int64_t(rows_per_wg), a.rows - r0));
-    TwiddleStage<THREADS> tws;
-    tws.load(a.tw, K);
+    const int ntw = K - a.rp.r[0];
+    TwiddleStage tws;
+    tws.load(a.tw, ntw);
     const float *slast = a.scale[a.d - 1];
-    if (coils_per_round >= C) {
-        const FastDiv byK(K), byN(N), byC(C);
-        // all coils of the rows in one tile (nr * C * K <= THREADS * kEPT
-        // elements, nr * N outputs): every load is issued before the first use.
-        // Lane rr (< nr <= 64) of every wavefront holds row rr's scaling factor.
-        RowScale rsf;
-        rsf.load(a.d, a.Nax, a.scale, int(r0) + min(int(threadIdx.x & 63), nr - 1));
-        const int nl = nr * C;
-        const int ne = nl * K;
-        float2 v[kEPT], pv[kEPT];
+    const int LS = lds_row(K);
+    float2 *x = a.x + (b * a.rows + r0) * N;
+    if constexpr (!COILS) {
+        const float2 *in = a.in + (b * a.rows + r0) * K;
+        auto load = [&](int lw, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+            constexpr int R = decltype(RC)::value;
+            const float2 *row = in + lw * K + j;
 #pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = min(int(threadIdx.x) + u * THREADS, ne - 1);  // (clamped: every load is in bounds)
-            const int lw = byK.div(e);
-            const int q = byK.rem(e, lw);
-            const int rr = byC.div(lw), cc = byC.rem(lw, rr);
-            v[u] = a.in[((b * C + cc) * a.rows + r0 + rr) * K + q];
-            if (a.phase) pv[u] = a.phase[q];
-        }
-        if (a.phase) {
+            for (int u = 0; u < R; ++u) v[u] = row[u * nbl];
 #pragma unroll
-            for (int u = 0; u < kEPT; ++u) v[u] = cmulcj(pv[u], v[u]);
-        }
-        tws.store(tw, K);
-#pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = threadIdx.x + u * THREADS;
-            if (e < ne) s[e] = v[u];
-        }
-        __syncthreads();
-        lds_fft<THREADS, true, false>(s, nl, K, K, 1, a.rp, tw);
-        const float rs = rsf.value();
-        const int no = nr * N;
-        float sv[kEPT];
-#pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = min(int(threadIdx.x) + u * THREADS, no - 1);
-            sv[u] = slast[byN.rem(e, byN.div(e))];
-        }
-        // values first (one wait for the scaling-factor loads), then the writes
-        float2 res[kEPT];
-#pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = min(int(threadIdx.x) + u * THREADS, no - 1);
-            const int rr = byN.div(e), i = byN.rem(e, rr);
-            const int q = pad_pos(i, N, K);
-            float2 sum = make_float2(0.f, 0.f);
-            if (a.coils) {
-#pragma unroll 1
-                for (int cc = 0; cc < C; ++cc)
-                    sum = cadd(sum, cmulcj(a.coils[(int64_t(cc) * a.rows + r0 + rr) * N + i], s[(rr * C + cc) * K + q]));
-            } else {
-#pragma unroll 1
-                for (int cc = 0; cc < C; ++cc) sum = cadd(sum, s[(rr * C + cc) * K + q]);
+            for (int u = 0; u < R; ++u) {
+                if (a.phase) v[u] = cmulcj(a.phase[j + u * nbl], v[u]);
+                v[u] = swap_if(true, v[u]);
             }
-            res[u] = cscale(sum, __shfl(rs, rr) * sv[u]);
-        }
+        };
+        leading_passes<false>(s, nr, LS, 1, a.rp, a.rp.n - 1, tw, load, [&]() NUFFT_INLINE { tws.store(tw, ntw); });
+        with_radix(a.rp.r[a.rp.n - 1], [&](auto RL) NUFFT_INLINE {
+            last_radix<RL, false>(s, nr, LS, 1, a.rp, tw, [&](int lw, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+                constexpr int R = decltype(RC)::value;
+                float sv[R];
 #pragma unroll
-        for (int u = 0; u < kEPT; ++u) {
-            const int e = threadIdx.x + u * THREADS;
-            const int rr = byN.div(min(e, no - 1)), i = e - __umul24(rr, N);
-            if (e < no) a.x[(b * a.rows + r0 + rr) * N + i] = res[u];
-        }
+                for (int u = 0; u < R; ++u) sv[u] = slast[max(src_row(j + u * nbl, N, K), 0)];
+                const float rs = row_scale(a.d, a.Nax, a.scale, int(r0) + lw);
+#pragma unroll
+                for (int u = 0; u < R; ++u) {
+                    if (dead_rows(u * nbl, nbl, N, K)) continue;
+                    const int i = src_row(j + u * nbl, N, K);
+                    if (i >= 0) x[lw * N + i] = cscale(swap_if(true, v[u]), rs * sv[u]);
+                }
+            });
+        });
         return;
     }
-    // more coils than one tile holds (C * K > the tile): rounds of
-    // coils_per_round coils summed in LDS accumulators after the tile
-    tws.store(tw, K);
-    if (threadIdx.x < nr) rsc[threadIdx.x] = row_scale(a.d, a.Nax, a.scale, int(r0) + threadIdx.x);
-    float2 *acc = s + rows_per_wg * coils_per_round * K;
-    for (int e = threadIdx.x; e < nr * N; e += THREADS) acc[e] = make_float2(0.f, 0.f);
+    // Coils: rounds of coils_per_round coils per row.  After the inverse passes
+    // every (line, pixel) is multiplied by the conjugate coil value, kCoilBatch
+    // per thread at a time (the first batch is loaded before the passes, which
+    // hide it), and the coils of a pixel are summed in coil order.  Several
+    // rounds keep the running sums in LDS after the tile.
+    constexpr int kCoilBatch = 4;
+    const FastDiv byN(N);
+    const int no = nr * N;
+    const bool rounds = coils_per_round < C;
+    float2 *acc = s + nr * coils_per_round * LS;
     for (int c0 = 0; c0 < C; c0 += coils_per_round) {
         const int nc = min(coils_per_round, C - c0);
         const int nl = nr * nc;
-        for (int e = threadIdx.x; e < nl * K; e += THREADS) {
-            const int lw = e / K, q = e - lw * K;
-            const int rr = lw / nc, cc = lw - rr * nc;
-            float2 v = a.in[((b * C + c0 + cc) * a.rows + r0 + rr) * K + q];
-            if (a.phase) v = cmulcj(a.phase[q], v);
-            s[e] = v;
-        }
-        __syncthreads();
-        lds_fft<THREADS, true, false>(s, nl, K, K, 1, a.rp, tw);
-        for (int e = threadIdx.x; e < nr * N; e += THREADS) {
-            const int rr = e / N, i = e - rr * N;
-            const int q = pad_pos(i, N, K);
-            float2 sum = make_float2(0.f, 0.f);
-            for (int cc = 0; cc < nc; ++cc) {
-                float2 t = s[(rr * nc + cc) * K + q];
-                if (a.coils) t = cmulcj(a.coils[(int64_t(c0 + cc) * a.rows + r0 + rr) * N + i], t);
-                sum = cadd(sum, t);
+        const FastDiv byC(nc);
+        float2 cv[kCoilBatch];
+        auto coil_batch = [&](int e0) NUFFT_INLINE {
+#pragma unroll
+            for (int u = 0; u < kCoilBatch; ++u) {
+                const int e = min(e0 + int(threadIdx.x) + u * int(blockDim.x), nl * N - 1);
+                const int lw = byN.div(e), i = byN.rem(e, lw);
+                const int rr = byC.div(lw), cc = byC.rem(lw, rr);
+                cv[u] = a.coils[(int64_t(c0 + cc) * a.rows + r0 + rr) * N + i];
             }
-            acc[e] = cadd(acc[e], sum);
+        };
+        if (a.coils) coil_batch(0);
+        auto load = [&](int lw, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
+            constexpr int R = decltype(RC)::value;
+            const int rr = byC.div(lw), cc = byC.rem(lw, rr);
+            const float2 *row = a.in + ((b * C + c0 + cc) * a.rows + r0 + rr) * K + j;
+#pragma unroll
+            for (int u = 0; u < R; ++u) v[u] = row[u * nbl];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                if (a.phase) v[u] = cmulcj(a.phase[j + u * nbl], v[u]);
+                v[u] = swap_if(true, v[u]);
+            }
+        };
+        if (c0 > 0) __syncthreads();  // the previous round's sums are read
+        leading_passes<false>(s, nl, LS, 1, a.rp, a.rp.n, tw, load, [&]() NUFFT_INLINE {
+            if (c0 == 0) tws.store(tw, ntw);
+        });
+        if (a.coils) {
+            for (int e0 = 0; e0 < nl * N; e0 += kCoilBatch * int(blockDim.x)) {
+                if (e0 > 0) coil_batch(e0);
+#pragma unroll
+                for (int u = 0; u < kCoilBatch; ++u) {
+                    const int e = e0 + int(threadIdx.x) + u * int(blockDim.x);
+                    if (e < nl * N) {
+                        const int lw = byN.div(e), i = byN.rem(e, lw);
+                        float2 *q = s + lw * LS + lds_row(grid_row(i, N, K));
+                        *q = cmulcj(cv[u], swap_if(true, *q));
+                    }
+                }
+            }
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    for (int e = threadIdx.x; e < nr * N; e += THREADS) {
-        const int rr = e / N, i = e - rr * N;
-        a.x[(b * a.rows + r0 + rr) * N + i] = cscale(acc[e], rsc[rr] * slast[i]);
+        for (int e = threadIdx.x; e < no; e += blockDim.x) {
+            const int rr = byN.div(e), i = byN.rem(e, rr);
+            const float2 *q = s + rr * nc * LS + lds_row(grid_row(i, N, K));
+            float2 sum = rounds && c0 > 0 ? acc[e] : make_float2(0.f, 0.f);
+            for (int cc = 0; cc < nc; ++cc) sum = cadd(sum, swap_if(!a.coils, q[cc * LS]));
+            if (c0 + nc < C)
+                acc[e] = sum;
+            else
+                x[e] = cscale(sum, row_scale(a.d, a.Nax, a.scale, int(r0) + rr) * slast[i]);
+        }
     }
 }
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_last_pass(LastPassArgs a, int rows_per_wg, int coils_per_round) {
-    last_pass_body<THREADS>(a, rows_per_wg, coils_per_round, blockIdx.x);
+template <bool COILS>
+__global__ __launch_bounds__(kFftThreads) void k_last_pass(LastPassArgs a, int rows_per_wg, int coils_per_round) {
+    last_pass_body<COILS>(a, rows_per_wg, coils_per_round, blockIdx.x);
 }
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_last_pass_multi(const LastJob *__restrict__ jobs,
+template <bool COILS>
+__global__ __launch_bounds__(kFftThreads) void k_last_pass_multi(const LastJob *__restrict__ jobs,
                                                             const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const LastJob &j = jobs[b.x];
-    last_pass_body<THREADS>(j.a, j.rpw, j.cpr, b.y);
+    last_pass_body<COILS>(j.a, j.rpw, j.cpr, b.y);
 }
 
-// FFT tile sizes: a tile holds up to THREADS * kEPT elements.  The host takes
+// FFT tile sizes: a tile holds up to kFftThreads * kEPT elements.  The host takes
 // the largest tile that still leaves about target_groups workgroups (small
 // transforms spread over the whole chip), then the smallest block that holds
 // it.
 
-template <template <int> class L, class A>
-hipError_t fft_dispatch(int threads, const A &a, hipStream_t s, int p0, int64_t p1, size_t lds, unsigned blocks) {
-    switch (threads) {
-        case 64: return L<64>::go(a, s, p0, p1, lds, blocks);
-        case 128: return L<128>::go(a, s, p0, p1, lds, blocks);
-        case 256: return L<256>::go(a, s, p0, p1, lds, blocks);
-        default: return L<512>::go(a, s, p0, p1, lds, blocks);
-    }
-}
+// LDS elements of one line (lds_row of its length).
+size_t line_lds(int K) { return size_t(lds_row(K)); }
 
 int threads_for(int elems) {
     int t = 64;
-    while (t < 512 && t * kEPT < elems) t *= 2;
+    while (t < kFftThreads && t * kEPT < elems) t *= 2;
     return t;
 }
-
-template <int T>
-struct FirstGo {
-    static hipError_t go(const FirstPassArgs &a, hipStream_t s, int lpw, int64_t, size_t lds, unsigned blocks) {
-        launch_kernel(k_first_pass<T>, dim3(blocks), dim3(T), lds, s, a, lpw);
-        return hipGetLastError();
-    }
-};
-
-template <int T>
-struct StridedGoF {
-    static hipError_t go(const StridedPassArgs &a, hipStream_t s, int W, int64_t ntc, size_t lds, unsigned blocks) {
-        launch_kernel((k_strided_pass<T, false, false>), dim3(blocks), dim3(T), lds, s, a, W, ntc);
-        return hipGetLastError();
-    }
-};
-
-template <int T>
-struct StridedGoI {
-    static hipError_t go(const StridedPassArgs &a, hipStream_t s, int W, int64_t ntc, size_t lds, unsigned blocks) {
-        if (a.split_of_tile)
-            launch_kernel((k_strided_pass<T, true, true>), dim3(blocks), dim3(T), lds, s, a, W, ntc);
-        else
-            launch_kernel((k_strided_pass<T, true, false>), dim3(blocks), dim3(T), lds, s, a, W, ntc);
-        return hipGetLastError();
-    }
-};
 
 }  // namespace
 
@@ -750,7 +809,7 @@ FftLaunch first_pass_launch(const FirstPassArgs &a, int threads) {
         lpw = int(std::max<int64_t>(1, std::min<int64_t>({total, kMaxLinesPerWg, threads * kEPT / a.K})));
     L.threads = threads > 0 ? threads : threads_for(lpw * a.K);
     L.blocks = (total + lpw - 1) / lpw;
-    L.lds = size_t(lpw + 1) * a.K * sizeof(float2);
+    L.lds = (size_t(a.K) + size_t(lpw) * line_lds(a.K)) * sizeof(float2);
     L.p0 = lpw;
     return L;
 }
@@ -758,7 +817,12 @@ FftLaunch first_pass_launch(const FirstPassArgs &a, int threads) {
 hipError_t launch_first_pass(const FirstPassArgs &a, hipStream_t s) {
     const FftLaunch L = first_pass_launch(a);
     if (L.blocks == 0) return hipSuccess;
-    return fft_dispatch<FirstGo>(L.threads, a, s, L.p0, 0, L.lds, unsigned(L.blocks));
+    const dim3 grid{unsigned(L.blocks)}, block{unsigned(L.threads)};
+    if (a.coils)
+        launch_kernel((k_first_pass<true>), grid, block, L.lds, s, a, L.p0);
+    else
+        launch_kernel((k_first_pass<false>), grid, block, L.lds, s, a, L.p0);
+    return hipGetLastError();
 }
 
 FftLaunch strided_pass_launch(const StridedPassArgs &a, int threads) {
@@ -775,28 +839,33 @@ FftLaunch strided_pass_launch(const StridedPassArgs &a, int threads) {
     const int64_t ntc = (a.inner + W - 1) / W;
     L.blocks = ntc * a.outer * a.grids;
     L.threads = threads > 0 ? threads : threads_for(int(W) * a.K);
-    L.lds = size_t(W + 1) * a.K * sizeof(float2);
+    L.lds = (size_t(a.K) + size_t(W) * line_lds(a.K)) * sizeof(float2);
     L.p0 = int(W);
     L.p1 = ntc;
     return L;
 }
 
+// A lane's byte offsets within its slab fit 32 bits in the first and last pass.
+bool strided_offsets_fit(const StridedPassArgs &a) {
+    const double slab = double(a.inner) * sizeof(float2);
+    return slab * a.rp.nbl[0] < 4294967296.0 && slab * a.rp.nbl[a.rp.n - 1] < 4294967296.0;
+}
+
 hipError_t launch_strided_pass(const StridedPassArgs &a, hipStream_t s) {
     const FftLaunch L = strided_pass_launch(a);
     if (L.blocks == 0) return hipSuccess;
-    if (a.inverse) return fft_dispatch<StridedGoI>(L.threads, a, s, L.p0, L.p1, L.lds, unsigned(L.blocks));
-    return fft_dispatch<StridedGoF>(L.threads, a, s, L.p0, L.p1, L.lds, unsigned(L.blocks));
+    if (!strided_offsets_fit(a)) return hipErrorInvalidValue;
+    const dim3 grid{unsigned(L.blocks)}, block{unsigned(L.threads)};
+    if (!a.inverse)
+        launch_kernel((k_strided_pass<false, kPlain>), grid, block, L.lds, s, a, L.p0, L.p1);
+    else if (a.split_of_tile)
+        launch_kernel((k_strided_pass<true, kSplitTiles>), grid, block, L.lds, s, a, L.p0, L.p1);
+    else if (a.mult)
+        launch_kernel((k_strided_pass<true, kProduct>), grid, block, L.lds, s, a, L.p0, L.p1);
+    else
+        launch_kernel((k_strided_pass<true, kPlain>), grid, block, L.lds, s, a, L.p0, L.p1);
+    return hipGetLastError();
 }
-
-namespace {
-template <int T>
-struct LastGo {
-    static hipError_t go(const LastPassArgs &a, hipStream_t s, int rpw, int64_t cpr, size_t lds, unsigned blocks) {
-        launch_kernel(k_last_pass<T>, dim3(blocks), dim3(T), lds, s, a, rpw, int(cpr));
-        return hipGetLastError();
-    }
-};
-}  // namespace
 
 FftLaunch last_pass_launch(const LastPassArgs &a, int threads) {
     FftLaunch L{64, 0, 0, 1, 1};
@@ -818,9 +887,8 @@ FftLaunch last_pass_launch(const LastPassArgs &a, int threads) {
     L.threads = threads > 0 ? threads : threads_for(rows_per_wg * coils_per_round * a.K);
     const int64_t nrt = (a.rows + rows_per_wg - 1) / rows_per_wg;
     L.blocks = nrt * a.B;
-    const bool one_round = coils_per_round >= a.C;
-    L.lds = (size_t(a.K) + size_t(rows_per_wg) * coils_per_round * a.K +
-             (one_round ? 0 : size_t(rows_per_wg) * a.N)) * sizeof(float2);
+    L.lds = (size_t(a.K) + size_t(rows_per_wg) * coils_per_round * line_lds(a.K) +
+             (coils_per_round < a.C ? size_t(rows_per_wg) * a.N : 0)) * sizeof(float2);
     L.p0 = rows_per_wg;
     L.p1 = coils_per_round;
     return L;
@@ -829,62 +897,48 @@ FftLaunch last_pass_launch(const LastPassArgs &a, int threads) {
 hipError_t launch_last_pass(const LastPassArgs &a, hipStream_t s) {
     const FftLaunch L = last_pass_launch(a);
     if (L.blocks == 0) return hipSuccess;
-    return fft_dispatch<LastGo>(L.threads, a, s, L.p0, L.p1, L.lds, unsigned(L.blocks));
+    const dim3 grid{unsigned(L.blocks)}, block{unsigned(L.threads)};
+    if (last_pass_coils(a))
+        launch_kernel((k_last_pass<true>), grid, block, L.lds, s, a, L.p0, int(L.p1));
+    else
+        launch_kernel((k_last_pass<false>), grid, block, L.lds, s, a, L.p0, int(L.p1));
+    return hipGetLastError();
 }
 
 // ---- many problems per launch
-namespace {
-template <int T>
-struct FirstMulti {
-    static void go(const FirstJob *j, const int4 *b, int64_t n, size_t lds, hipStream_t s) {
-        launch_kernel(k_first_pass_multi<T>, dim3(unsigned(n)), dim3(T), lds, s, j, b);
-    }
-};
-template <int T>
-struct LastMulti {
-    static void go(const LastJob *j, const int4 *b, int64_t n, size_t lds, hipStream_t s) {
-        launch_kernel(k_last_pass_multi<T>, dim3(unsigned(n)), dim3(T), lds, s, j, b);
-    }
-};
-template <bool INV, bool SPLIT>
-struct StridedMultiF {
-    template <int T>
-    struct K {
-        static void go(const StridedJob *j, const int4 *b, int64_t n, size_t lds, hipStream_t s) {
-            launch_kernel((k_strided_pass_multi<T, INV, SPLIT>), dim3(unsigned(n)), dim3(T), lds, s, j, b);
-        }
-    };
-};
-
-template <template <int> class L, class Job>
-hipError_t threads_go(int threads, const Job *j, const int4 *b, int64_t n, size_t lds, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    switch (threads) {
-        case 64: L<64>::go(j, b, n, lds, s); break;
-        case 128: L<128>::go(j, b, n, lds, s); break;
-        case 256: L<256>::go(j, b, n, lds, s); break;
-        case 512: L<512>::go(j, b, n, lds, s); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-}  // namespace
-
-hipError_t launch_first_pass_multi(const FirstJob *jobs, const int4 *blocks, int64_t nblocks, int threads,
+hipError_t launch_first_pass_multi(const FirstJob *jobs, const int4 *blocks, int64_t nblocks, int threads, bool coils,
                                    size_t lds, hipStream_t s) {
-    return threads_go<FirstMulti>(threads, jobs, blocks, nblocks, lds, s);
+    if (nblocks == 0) return hipSuccess;
+    const dim3 grid{unsigned(nblocks)}, block{unsigned(threads)};
+    if (coils)
+        launch_kernel((k_first_pass_multi<true>), grid, block, lds, s, jobs, blocks);
+    else
+        launch_kernel((k_first_pass_multi<false>), grid, block, lds, s, jobs, blocks);
+    return hipGetLastError();
 }
 
 hipError_t launch_strided_pass_multi(const StridedJob *jobs, const int4 *blocks, int64_t nblocks, int threads,
                                      bool inverse, bool split, size_t lds, hipStream_t s) {
-    if (!inverse) return threads_go<StridedMultiF<false, false>::K>(threads, jobs, blocks, nblocks, lds, s);
-    if (split) return threads_go<StridedMultiF<true, true>::K>(threads, jobs, blocks, nblocks, lds, s);
-    return threads_go<StridedMultiF<true, false>::K>(threads, jobs, blocks, nblocks, lds, s);
+    if (nblocks == 0) return hipSuccess;
+    const dim3 grid{unsigned(nblocks)}, block{unsigned(threads)};
+    if (!inverse)
+        launch_kernel((k_strided_pass_multi<false, kPlain>), grid, block, lds, s, jobs, blocks);
+    else if (split)
+        launch_kernel((k_strided_pass_multi<true, kSplitTiles>), grid, block, lds, s, jobs, blocks);
+    else
+        launch_kernel((k_strided_pass_multi<true, kPlain>), grid, block, lds, s, jobs, blocks);
+    return hipGetLastError();
 }
 
-hipError_t launch_last_pass_multi(const LastJob *jobs, const int4 *blocks, int64_t nblocks, int threads, size_t lds,
-                                  hipStream_t s) {
-    return threads_go<LastMulti>(threads, jobs, blocks, nblocks, lds, s);
+hipError_t launch_last_pass_multi(const LastJob *jobs, const int4 *blocks, int64_t nblocks, int threads, bool coils,
+                                  size_t lds, hipStream_t s) {
+    if (nblocks == 0) return hipSuccess;
+    const dim3 grid{unsigned(nblocks)}, block{unsigned(threads)};
+    if (coils)
+        launch_kernel((k_last_pass_multi<true>), grid, block, lds, s, jobs, blocks);
+    else
+        launch_kernel((k_last_pass_multi<false>), grid, block, lds, s, jobs, blocks);
+    return hipGetLastError();
 }
 
 }  // namespace nufft

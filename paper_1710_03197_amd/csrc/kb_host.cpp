@@ -5,6 +5,7 @@
 // GPU evaluates, FFT twiddles and the radix schedule of the oversampled FFT
 // (Section 2.1 "Oversampled FFT").
 #include <algorithm>
+#include <numeric>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -297,40 +298,86 @@ std::vector<float> kb_scaling(int N, int K, int J, double beta) {
     return s;
 }
 
-std::vector<float2> twiddles(int K) {
-    std::vector<float2> tw(K);
-    for (int e = 0; e < K; ++e) {
-        double ang = 2.0 * kPi * double(e) / double(K);
-        tw[e] = make_float2(float(std::cos(ang)), float(-std::sin(ang)));
+namespace {
+// Best factorisation of rem into radices <= most (non-increasing): fewest
+// factors, then the smallest sum.
+void best_radices(int rem, int most, std::vector<int> &cur, std::vector<int> &best) {
+    static const int kRadices[] = {8, 6, 5, 4, 3, 2};
+    auto sum = [](const std::vector<int> &v) { return std::accumulate(v.begin(), v.end(), 0); };
+    if (rem == 1) {
+        if (best.empty() || cur.size() < best.size() || (cur.size() == best.size() && sum(cur) < sum(best))) best = cur;
+        return;
     }
-    return tw;
+    if (!best.empty() && cur.size() + 1 > best.size()) return;
+    for (int r : kRadices) {
+        if (r > most || rem % r) continue;
+        cur.push_back(r);
+        best_radices(rem / r, r, cur, best);
+        cur.pop_back();
+    }
 }
+}  // namespace
 
 bool radix_plan(int K, RadixPlan *rp, int schedule) {
-    rp->n = 0;
-    int rem = K;
-    // radices taken greedily in this order (schedule 3: schedule 0's passes
-    // run in reverse)
-    static const int orders[3][5] = {{8, 4, 2, 3, 5}, {4, 8, 2, 3, 5}, {3, 5, 8, 4, 2}};
+    *rp = RadixPlan{};
     if (schedule < 0 || schedule > 3) return false;
-    for (int r : orders[schedule == 3 ? 0 : schedule]) {
-        while (rem % r == 0) {
-            if (rp->n >= kMaxPasses) return false;
-            rp->r[rp->n++] = r;
-            rem /= r;
-        }
+    std::vector<int> r;
+    if (schedule == 0) {
+        std::vector<int> cur;
+        best_radices(K, 8, cur, r);
+        if (r.empty()) return false;
+        // a radix that divides the pass's zero rows off whole (a multiple of
+        // 4 at twofold oversampling) first and last, odd radices between
+        std::stable_sort(r.begin(), r.end(), [](int x, int y) { return (x % 4 == 0) > (y % 4 == 0); });
+        if (r.size() > 2 && r[1] % 4 == 0) std::swap(r[1], r.back());
+    } else {
+        static const int orders[3][5] = {{4, 8, 2, 3, 5}, {3, 5, 8, 4, 2}, {8, 4, 2, 3, 5}};
+        int rem = K;
+        for (int q : orders[schedule - 1])
+            while (rem % q == 0) {
+                r.push_back(q);
+                rem /= q;
+            }
+        if (rem != 1) return false;
+        if (schedule == 3) std::reverse(r.begin(), r.end());
     }
-    if (rem != 1) return false;
-    if (schedule == 3) std::reverse(rp->r, rp->r + rp->n);
+    if (r.size() == 1) r.push_back(1);
+    if (int(r.size()) > kMaxPasses) return false;
+    // long lines start and end with a radix of at least 4: the strided passes
+    // address K / r rows by 32-bit offsets, which then reach any grid
+    if (K > 64) {
+        auto wide = [&](int q) { return q >= 4; };
+        if (!wide(r.front()))
+            if (auto it = std::find_if(r.begin() + 1, r.end(), wide); it != r.end()) std::iter_swap(r.begin(), it);
+        if (!wide(r.back()))
+            if (auto it = std::find_if(r.begin() + 1, r.end(), wide); it != r.end()) std::iter_swap(r.end() - 1, it);
+    }
     auto magic = [](int D) { return D > 1 ? 0xFFFFFFFFu / unsigned(D) + 1u : 0u; };
-    int Ns = 1;
+    rp->n = int(r.size());
+    int Ns = 1, off = 0;
     for (int p = 0; p < rp->n; ++p) {
-        rp->span[p] = K / (Ns * rp->r[p]);
+        rp->r[p] = r[p];
+        rp->ns[p] = Ns;
+        rp->nbl[p] = K / r[p];
         rp->m_ns[p] = magic(Ns);
-        rp->m_nbl[p] = magic(K / rp->r[p]);
-        Ns *= rp->r[p];
+        rp->m_nbl[p] = magic(K / r[p]);
+        rp->tw_off[p] = off;
+        if (p > 0) off += (r[p] - 1) * Ns;
+        Ns *= r[p];
     }
     return true;
+}
+
+std::vector<float2> pass_twiddles(int K, const RadixPlan &rp) {
+    std::vector<float2> tw;
+    tw.reserve(size_t(K));
+    for (int p = 1; p < rp.n; ++p)
+        for (int r = 1; r < rp.r[p]; ++r)
+            for (int k = 0; k < rp.ns[p]; ++k) {
+                const double ang = 2.0 * kPi * double(r * k) / double(rp.ns[p] * rp.r[p]);
+                tw.push_back(make_float2(float(std::cos(ang)), float(-std::sin(ang))));
+            }
+    return tw;
 }
 
 }  // namespace nufft

@@ -13,9 +13,10 @@ namespace nufft {
 
 constexpr int kMaxDim = 3;
 constexpr int kMaxJ = 16;
-constexpr int kMaxPasses = 16;     // radix passes per axis (K <= 4096)
+constexpr int kMaxPasses = 12;     // radix passes per axis (K <= 4096: at most 2 * 2^11)
 constexpr int kMaxNeighbors = 27;  // bins whose windows can reach one tile
-constexpr int kFftTileElems = 4096;  // complex elements of the largest FFT workgroup tile (512 threads x 8)
+constexpr int kFftThreads = 512;     // threads of the largest FFT workgroup
+constexpr int kFftTileElems = 4096;  // complex elements of its tile (8 per thread)
 constexpr int kXcds = 8;             // XCDs the hardware deals workgroups over, each with its own L2
 constexpr int kMaxLinesPerWg = 64;   // lines (contiguous-axis passes) per FFT workgroup
 constexpr int kMaxPolyDeg = 23;
@@ -23,15 +24,17 @@ constexpr int kInterpSamplesPerThread = 2;  // gather work item = 512 samples
 constexpr int kLdsBudget = 64 * 1024;      // bytes of LDS a gather or gridding tile may use
 constexpr int kInterpLdsBudget = 64 * 1024;  // bytes of LDS a gather item covering several tiles may use
 
-// Radix schedule of one FFT axis (Stockham, product of r[] == K).
-// Per pass p (Ns = r[0] ... r[p-1] the length of the sub-transforms done so
-// far): span = K / (Ns r[p]), and the division magics ceil(2^32 / D) of
-// D = Ns and D = K / r[p] (0 for D = 1) the passes use instead of integer
-// divisions.
+// Radix schedule of one FFT axis (Stockham, product of r[] == K, n >= 2: a
+// length of one radix gets a pass of radix 1 after it).  Per pass p: ns = r[0]
+// ... r[p-1] the length of the sub-transforms done so far, nbl = K / r[p] its
+// butterflies, the division magics ceil(2^32 / D) of both (0 for D = 1), and
+// the offset of its twiddles in the axis table (pass_twiddles).
 struct RadixPlan {
     int n;
     int r[kMaxPasses];
-    int span[kMaxPasses];
+    int ns[kMaxPasses];
+    int nbl[kMaxPasses];
+    int tw_off[kMaxPasses];
     unsigned m_ns[kMaxPasses];
     unsigned m_nbl[kMaxPasses];
 };
@@ -74,12 +77,13 @@ std::vector<float> minmax_scaling(int N, int K, int J, double beta);
 std::vector<float2> half_phase(int K);
 // Scaling table s(i) = 1 / Phi((i - N/2)/K), i in [0, N) (float32).
 std::vector<float> kb_scaling(int N, int K, int J, double beta);
-// Twiddles e^{-2 pi i e / K}, e in [0, K), computed in float64.
-std::vector<float2> twiddles(int K);
 // Stockham radix schedule; false if K has a prime factor above 5.  schedule
-// 0: radices 8, 4, 2, 3, 5 taken greedily in that order (the default); 1: 4,
-// 8, 2, 3, 5; 2: 3, 5, 8, 4, 2; 3: schedule 0 with its passes reversed.
+// 0: the fewest passes over radices 2..6 and 8, then the smallest sum of radices (the default); 1: 4, 8, 2, 3, 5 taken greedily in
+// that order; 2: 3, 5, 8, 4, 2; 3: 5, 3, 2, 4, 8.
 bool radix_plan(int K, RadixPlan *rp, int schedule = 0);
+// Twiddles of the passes after the first, K - r[0] of them, computed in
+// float64: pass p holds e^{-2 pi i r k / (ns r[p])} as [r = 1 .. r[p]-1][k < ns].
+std::vector<float2> pass_twiddles(int K, const RadixPlan &rp);
 
 // ---- device kernel launchers (the .hip files).  All asynchronous on `s`.
 
@@ -150,6 +154,8 @@ struct LastPassArgs {
     const float2 *phase;  // min-max grid phase e^{-i pi k / K} of this pass's axis (nullptr: none)
 };
 hipError_t launch_last_pass(const LastPassArgs &a, hipStream_t s);
+// Whether a last pass combines coils (its own kernel instances).
+inline bool last_pass_coils(const LastPassArgs &a) { return a.coils != nullptr || a.C > 1; }
 
 // Geometry shared by the sample kernels.
 struct SampleGeom {
@@ -442,12 +448,12 @@ struct PermuteJob {
     int grids;
     float2 *ys;
 };
-hipError_t launch_first_pass_multi(const FirstJob *jobs, const int4 *blocks, int64_t nblocks, int threads,
+hipError_t launch_first_pass_multi(const FirstJob *jobs, const int4 *blocks, int64_t nblocks, int threads, bool coils,
                                    size_t lds, hipStream_t s);
 hipError_t launch_strided_pass_multi(const StridedJob *jobs, const int4 *blocks, int64_t nblocks, int threads,
                                      bool inverse, bool split, size_t lds, hipStream_t s);
-hipError_t launch_last_pass_multi(const LastJob *jobs, const int4 *blocks, int64_t nblocks, int threads, size_t lds,
-                                  hipStream_t s);
+hipError_t launch_last_pass_multi(const LastJob *jobs, const int4 *blocks, int64_t nblocks, int threads, bool coils,
+                                  size_t lds, hipStream_t s);
 // LDS of a staged gather launch (0 for the direct form).
 size_t interp_lds(const InterpArgs &a);
 hipError_t launch_interp_multi(const InterpArgs *jobs, const int4 *blocks, int64_t nblocks, int J, int d,
