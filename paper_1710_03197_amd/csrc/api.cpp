@@ -754,6 +754,8 @@ int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s,
     a.items = p->staged_interp ? p->iitems : nullptr;
     a.n_items = p->n_iitems;
     a.merge = p->interp_merge;
+    // (in a multi-problem launch the other problems fill the chip)
+    a.grids_per_wg = a.items && !col ? interp_grids_per_wg(a.n_items, grids) : grids;
     for (int ax = 0; ax < p->d; ++ax) {
         a.T[ax] = p->T[ax];
         a.nt[ax] = p->nt[ax];

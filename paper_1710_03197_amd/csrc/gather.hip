@@ -17,7 +17,7 @@ namespace {
 // every sample of the item (window base inside the tiles) reads its J^d taps
 // from LDS.
 template <int J, int DIM>
-__device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item) {
+__device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, int gg) {
     extern __shared__ float2 reg[];
     const InterpItem it = a.items[item];
     int tc[DIM], base[DIM], E[DIM];
@@ -118,7 +118,8 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item) {
     const int pc = H <= 256 ? int(threadIdx.x) - pr0 * H : int(threadIdx.x);
     int kl = base[DIM - 1] + 2 * pc;  // grid column of the pair (< 2 K_last)
     if (kl >= KL) kl -= KL;
-    for (int g = 0; g < a.grids; ++g) {
+    const int g_lo = gg * a.grids_per_wg, g_hi = min(a.grids, g_lo + a.grids_per_wg);
+    for (int g = g_lo; g < g_hi; ++g) {
         const float2 *G = a.G + int64_t(g) * a.grid_elems;
         __syncthreads();
         constexpr int U = 8;  // loads in flight per thread
@@ -224,14 +225,14 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item) {
 
 template <int J, int DIM>
 __global__ __launch_bounds__(256) void k_interp(InterpArgs a) {
-    interp_body<J, DIM>(a, blockIdx.x);
+    interp_body<J, DIM>(a, blockIdx.x, blockIdx.y);
 }
 
 template <int J, int DIM>
 __global__ __launch_bounds__(256) void k_interp_multi(const InterpArgs *__restrict__ jobs,
                                                      const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
-    interp_body<J, DIM>(jobs[b.x], b.y);
+    interp_body<J, DIM>(jobs[b.x], b.y, 0);
 }
 
 // Gather straight from the grid (L1/L2), one thread per sorted sample: used
@@ -414,7 +415,8 @@ struct InterpLaunch {
         if (a.M == 0) return hipSuccess;
         if (a.items) {
             if (a.n_items == 0) return hipSuccess;
-            launch_kernel((k_interp<J, DIM>), dim3(unsigned(a.n_items)), dim3(256), interp_lds(a), s, a);
+            const unsigned gy = unsigned((a.grids + a.grids_per_wg - 1) / a.grids_per_wg);
+            launch_kernel((k_interp<J, DIM>), dim3(unsigned(a.n_items), gy), dim3(256), interp_lds(a), s, a);
         } else {
             const int64_t blocks = (a.M + 255) / 256;
             launch_kernel((k_interp_direct<J, DIM>), dim3(unsigned(blocks)), dim3(256), 0, s, a);
