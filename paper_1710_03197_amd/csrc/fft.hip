@@ -70,18 +70,18 @@ __device__ __forceinline__ void dft<8>(float2 *v) {
     float2 o[4] = {v[1], v[3], v[5], v[7]};
     dft<4>(e);
     dft<4>(o);
-    // o[k] *= e^{-2 pi i k / 8}
-    float2 o1 = make_float2((o[1].x + o[1].y) * r2, (o[1].y - o[1].x) * r2);
-    float2 o2 = mul_negi(o[2]);
-    float2 o3 = make_float2((o[3].y - o[3].x) * r2, -(o[3].x + o[3].y) * r2);
+    // o[k] *= e^{-2 pi i k / 8}, folded into the sums by fused products
+    const float2 t1 = make_float2(o[1].x + o[1].y, o[1].y - o[1].x);
+    const float2 o2 = mul_negi(o[2]);
+    const float2 t3 = make_float2(o[3].y - o[3].x, -(o[3].x + o[3].y));
     v[0] = cadd(e[0], o[0]);
     v[4] = csub(e[0], o[0]);
-    v[1] = cadd(e[1], o1);
-    v[5] = csub(e[1], o1);
+    v[1] = make_float2(fmaf(t1.x, r2, e[1].x), fmaf(t1.y, r2, e[1].y));
+    v[5] = make_float2(fmaf(-t1.x, r2, e[1].x), fmaf(-t1.y, r2, e[1].y));
     v[2] = cadd(e[2], o2);
     v[6] = csub(e[2], o2);
-    v[3] = cadd(e[3], o3);
-    v[7] = csub(e[3], o3);
+    v[3] = make_float2(fmaf(t3.x, r2, e[3].x), fmaf(t3.y, r2, e[3].y));
+    v[7] = make_float2(fmaf(-t3.x, r2, e[3].x), fmaf(-t3.y, r2, e[3].y));
 }
 
 // Composite radices R = A B: A-point DFTs over n1 of n = B n1 + n2, the factors

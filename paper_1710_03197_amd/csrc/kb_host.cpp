@@ -329,7 +329,7 @@ bool radix_plan(int K, RadixPlan *rp, int schedule) {
         // a radix that divides the pass's zero rows off whole (a multiple of
         // 4 at twofold oversampling) first and last, odd radices between
         std::stable_sort(r.begin(), r.end(), [](int x, int y) { return (x % 4 == 0) > (y % 4 == 0); });
-        if (r.size() > 2 && r[1] % 4 == 0) std::swap(r[1], r.back());
+        if (r.size() > 2 && r.back() % 4 && r[1] % 4 == 0) std::swap(r[1], r.back());
     } else {
         static const int orders[3][5] = {{4, 8, 2, 3, 5}, {3, 5, 8, 4, 2}, {8, 4, 2, 3, 5}};
         int rem = K;
