@@ -142,6 +142,7 @@ struct nufft_plan_s {
     bool presort = false;      // gridding reads samples permuted into sorted order
     bool fuse_reduce = false;  // first inverse FFT pass sums the partial tiles
     bool grid_mfma = false;    // gridding on the matrix cores by row tiles
+    bool grid_cols = false;    // 2D tiles the column form of several grids takes
     bool grid_blk = false;     // 3D gridding on the matrix cores by 4 x 4 blocks
     int grid_waves = 4;        // its wavefronts per work item (1 or 4)
     int rec_stride = 0;        // its LDS floats per staged sample
@@ -815,7 +816,9 @@ int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s
     {
         int tsum = 0;
         for (int ax = 0; ax < p->d; ++ax) tsum += p->T[ax];
-        a.grids_per_wg = p->grid_mfma ? grid_grids_per_wg(grids, p->tile_cells, tsum) : 1;
+        a.cols = p->grid_cols ? grid_cols_waves(p->n_items, p->M, grids, p->chunk, col != nullptr) : 0;
+        if (a.cols) a.mfma = 0;
+        a.grids_per_wg = a.mfma ? grid_grids_per_wg(grids, p->tile_cells, tsum) : 1;
     }
     if (col)
         col->add(kSlotGrid, kStGrid).grid = a;
@@ -971,8 +974,7 @@ void stage_blocks(const Emitted &em, int job, int threads, std::vector<int4> &ou
         }
         case kStGrid: {
             const GridArgs &a = em.grid;
-            const int gp = a.mfma ? a.grids_per_wg : 1;
-            for (int g = 0; g < (a.grids + gp - 1) / gp; ++g)
+            for (int g = 0; g < grid_groups(a); ++g)
                 for (int64_t b = 0; b < a.n_items; ++b) out.push_back(make_int4(job, int(b), g, 0));
             break;
         }
@@ -1512,9 +1514,10 @@ int nufft_plan_ex(int d, const int64_t *N, const int64_t *K, int J, int64_t M, c
         p->K[a] = K[a];
     }
     // kernel, scaling and FFT constants per axis
-    // tile edges: the last axis (one register row per lane in the gridding) at
-    // most 32 cells, the leading axes at most 64 rows in all
-    const int targets[3][3] = {{32, 1, 1}, {32, 16, 1}, {8, 8, 16}};
+    // tile edges (measured in 2D, 32 x 16 -> 16 x 16: 64 x 64 image 46.4 -> 45.1 us
+    // a pair, every tuned workload takes 16 x 16, and the column form of several
+    // grids needs it)
+    const int targets[3][3] = {{32, 1, 1}, {16, 16, 1}, {8, 8, 16}};
     const int need = J - 1;
     p->tile_cells = 1;
     p->nbins = 1;
@@ -1610,6 +1613,7 @@ int nufft_plan_ex(int d, const int64_t *N, const int64_t *K, int J, int64_t M, c
             return bail(fail(NUFFT_ERR_UNSUPPORTED,
                              "matrix-core gridding needs T_last = 16, 16, 32 or 64 rows and sum(T) <= 61"));
         p->grid_mfma = !p->grid_blk && mfma_ok && !(opt && opt->grid_mfma == 2);
+        p->grid_cols = p->grid_mfma && d == 2 && p->T[0] == 16 && !(opt && opt->grid_mfma == 3);
     }
     {
         const int64_t region = interp_region_elems(d, p->T, J, 1) * int64_t(sizeof(float2));

@@ -1,5 +1,7 @@
 // Gridding V^H (paper Section 2.1 "Adjoint PyNUFFT"):
 //   k_grid_blk     in 3D on the matrix cores by 4 x 4 blocks;
+//   k_grid_cols    in 2D for several grids, by 4 x 4 blocks with the grids as
+//                  columns;
 //   k_grid_mfma    by row tiles (2D and other 16-cell tiles);
 //   k_grid         on the vector ALUs (other tiles).  All output driven: a
 //                  work item owns one grid tile and walks the samples that
@@ -538,6 +540,214 @@ __global__ __launch_bounds__(256) void k_grid_mfma_multi(const GridArgs *__restr
     grid_mfma_body<DIM, NJ, MB, GP, TAB>(jobs[b.x], b.y, b.z);
 }
 
+// V^H on the matrix cores in 2D for several grids (coils, batch entries) that
+// share the trajectory: 16 x 16 tiles, one wavefront per work item and group of
+// kColGrids grids.  The tile is cut into 4 x 4 blocks, and a block is one
+// product over the samples whose columns are the grids' real and imaginary
+// parts:
+//   H[(x0, x1)][2 g + part] = sum_s (w0_s[x0] w1_s[x1]) v_{s,g,part}
+// (v_mfma_f32_16x16x4_f32; eight grids fill its 16 columns).  A J = 6 window
+// covers 36 of the 81 cells of the blocks it reaches on average, against 36 of
+// 256 in the row-tile form, whose columns are cells, and a product serves eight
+// grids.  Staging is the block kernel's: 64 samples per batch (weights spread
+// over the tile, taps outside it to a discard slot, the set of blocks reached),
+// then block by block the groups of four samples that reach it.  Bound by LDS
+// latency and reads (four per two products) and the staging.  Measured, row-tile
+// form -> this: 8 grids of 640 x 640, M = 128000: 72 -> 38 us; 24 grids of 256 x
+// 256, M = 20011: 54 -> 31 us; 24 spirals x 8 coils: 1215 -> 447 us.
+template <int NJ, bool TAB, int NW>
+__device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, int gg) {
+    constexpr int T = 16, NBLK = 16;
+    constexpr int RS = 2 * T + 1;            // weights of a sample, then the discard slot (odd)
+    constexpr int VS = 2 * kColGrids + 1;    // its values (odd)
+    extern __shared__ float col_lds[];
+    __shared__ int seg_lo[kMaxNeighbors + 1];
+    __shared__ int seg_pre[kMaxNeighbors + 1];
+    const GridItem it = a.items[item];
+    const int nseg = grid_item_segments(a, item, seg_lo, seg_pre);
+    const int J = a.geo.J;
+    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    float *rec = col_lds + wave * 64 * (RS + VS + 1);                 // [64][RS]
+    float *val = rec + 64 * RS;                                       // [64][VS]
+    unsigned *smask = reinterpret_cast<unsigned *>(val + 64 * VS);    // [64]
+    const int t0 = it.tile / a.nt[1];
+    const int base[2] = {t0 * T, (it.tile - t0 * a.nt[1]) * T};
+    const int total = seg_pre[nseg];
+    const int f0 = it.chunk * a.chunk;
+    const int n = min(total, f0 + a.chunk) - f0;
+    const int g0 = gg * kColGrids;
+    const int ng = min(kColGrids, a.grids - g0);
+    const int rl = lane & 15, kq = lane >> 4;
+    mfma_f4 acc[NBLK];
+#pragma unroll
+    for (int q = 0; q < NBLK; ++q) acc[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
+    // trajectory (or window record) and values of this lane's next sample,
+    // loaded one batch ahead
+    float pom[TAB ? 1 : 2];
+    float4 prec[TAB ? table_f4(2, NJ) : 1];
+    float2 pv[kColGrids];
+    bool pvalid = false;
+    int cursor = 0;
+    auto fetch = [&](int b) {
+        const int s_idx = b + wave * 64 + lane;
+        pvalid = s_idx < n;
+        const int sg = batch_segment(seg_pre, nseg, cursor, f0 + b + wave * 64, 64, f0 + s_idx);
+        if (pvalid) {
+            const int64_t i = seg_lo[sg] + (f0 + s_idx - seg_pre[sg]);
+            if constexpr (TAB) {
+                load_window_record<NJ, 2>(a.geo, i, prec);
+            } else {
+#pragma unroll
+                for (int ax = 0; ax < 2; ++ax) pom[ax] = a.om_sorted[i * 2 + ax];
+            }
+            const float2 *y = a.y + int64_t(g0) * a.M + (a.y_sorted ? i : int64_t(a.perm[i]));
+#pragma unroll
+            for (int q = 0; q < kColGrids; ++q) pv[q] = q < ng ? y[int64_t(q) * a.M] : make_float2(0.f, 0.f);
+        }
+    };
+    fetch(0);
+    for (int b0 = 0; b0 < n; b0 += 64 * NW) {
+        {
+            float4 *z = reinterpret_cast<float4 *>(rec);
+            for (int e = lane; e < 16 * RS; e += 64) z[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        group_sync(64);
+        // ---- stage this lane's sample
+        unsigned mk = 0;
+        float2 ph = make_float2(1.f, 0.f);
+        if constexpr (!TAB)
+            if (pvalid && a.geo.minmax) ph = mm_phase<2>(a.geo, pom);
+#pragma unroll
+        for (int q = 0; q < kColGrids; ++q) {
+            const float2 v = pvalid ? (a.geo.minmax ? cmulcj(ph, pv[q]) : pv[q]) : make_float2(0.f, 0.f);
+            val[lane * VS + 2 * q] = v.x;
+            val[lane * VS + 2 * q + 1] = v.y;
+        }
+        if (pvalid) {
+            float *my = rec + lane * RS;
+            int kwa[2];
+            float wva[2][NJ];
+            if constexpr (TAB)
+                unpack_window<NJ, 2>(prec, kwa, wva);
+            else
+                eval_window<NJ, 2>(a.geo, pom, kwa, wva);
+            unsigned bm[2] = {0u, 0u};
+#pragma unroll
+            for (int ax = 0; ax < 2; ++ax) {
+                const int K = a.geo.K[ax];
+                float *wv = wva[ax];
+                if (a.geo.minmax) mm_sign_taps<NJ>(wv, K - kwa[ax]);
+                // first tap relative to the tile; windows wrapping in from the
+                // top of the axis come in negative (an axis of one tile wraps
+                // inside it instead)
+                int o = kwa[ax] - base[ax];
+                const bool one = a.nt[ax] == 1;
+                if (!one && o >= T) o -= K;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    int x = o + j;
+                    if (one && x >= K) x -= K;
+                    const bool in = unsigned(x) < unsigned(T) && j < J;
+                    my[in ? ax * T + x : 2 * T] = wv[j];
+                    bm[ax] |= in ? 1u << (x >> 2) : 0u;
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                if ((bm[0] >> b) & 1u) mk |= bm[1] << (4 * b);
+        }
+        smask[lane] = mk;
+        if (b0 + 64 * NW < n) fetch(b0 + 64 * NW);
+        group_sync(64);
+        // ---- walk: lane l < 16 looks at samples 4 l .. 4 l + 3.  Two blocks
+        // side by side at a time (they share the values and the row weights,
+        // and their products are independent), two groups of samples per step.
+        unsigned gm = 0;
+        if (lane < 16) {
+            const uint4 m4 = reinterpret_cast<const uint4 *>(smask)[lane];
+            gm = m4.x | m4.y | m4.z | m4.w;
+        }
+#pragma unroll
+        for (int q = 0; q < NBLK; q += 2) {
+            const int a0 = 4 * (q / 4) + (rl >> 2);
+            const int a1 = T + 4 * (q % 4) + (rl & 3);
+            uint64_t act = __ballot(((gm >> q) & 3u) != 0u);
+            while (act) {
+                const int i0 = int(__builtin_ctzll(act));
+                act &= act - 1;
+                const bool two = act != 0;
+                const int i1 = two ? int(__builtin_ctzll(act)) : i0;
+                act &= act - 1;
+                const float *s0 = rec + (4 * i0 + kq) * RS, *s1 = rec + (4 * i1 + kq) * RS;
+                const float v0 = val[(4 * i0 + kq) * VS + rl], v1 = val[(4 * i1 + kq) * VS + rl];
+                const float r0 = s0[a0], c0 = s0[a1], d0 = s0[a1 + 4], r1 = s1[a0], c1 = s1[a1], d1 = s1[a1 + 4];
+                const float w1 = two ? v1 : 0.f;
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(r0 * c0, v0, acc[q], 0, 0, 0);
+                acc[q + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(r0 * d0, v0, acc[q + 1], 0, 0, 0);
+                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * c1, w1, acc[q], 0, 0, 0);
+                acc[q + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * d1, w1, acc[q + 1], 0, 0, 0);
+            }
+        }
+        group_sync(64);
+    }
+    // ---- write the tile.  D[i][j] of block q sits in lane j + 16 (i / 4),
+    // register i % 4: the lane holds part j & 1 of grid j / 2 at row x0 = 4
+    // (q / 4) + lane / 16, columns x1 = 4 (q % 4) + register.  Neighbouring
+    // lanes swap halves, so each stores two whole cells (16 bytes: tiles, grids
+    // and partial tiles start at even cells).
+    const bool to_partial = it.nchunks > 1;
+    const int g = g0 + (rl >> 1);
+    const bool odd = rl & 1;
+    float2 *dst = to_partial ? a.partials + (int64_t(g) * a.n_slots + it.slot + it.chunk) * a.tile_cells
+                             : a.h + int64_t(g) * a.grid_elems;
+    const int64_t pitch = to_partial ? T : a.geo.K[1];
+    const int64_t first = to_partial ? 0 : int64_t(base[0]) * a.geo.K[1] + base[1];
+    auto swap_lane = [](float v) {  // the value of lane ^ 1
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+    };
+    auto store_block = [&](int q, mfma_f4 v) {
+        const float u0 = swap_lane(odd ? v[0] : v[2]), u1 = swap_lane(odd ? v[1] : v[3]);
+        const float4 cells = odd ? make_float4(u0, v[2], u1, v[3]) : make_float4(v[0], u0, v[1], u1);
+        const int64_t idx = first + (4 * (q >> 2) + kq) * pitch + 4 * (q & 3) + (odd ? 2 : 0);
+        if (g - g0 < ng) *reinterpret_cast<float4 *>(dst + idx) = cells;
+    };
+    if constexpr (NW == 1) {
+#pragma unroll
+        for (int q = 0; q < NBLK; ++q) store_block(q, acc[q]);
+    } else {
+        // the wavefronts' blocks are summed in wave order through LDS, half of
+        // them at a time; wavefront w sums and stores every NW-th block
+        constexpr int HB = NBLK / 2;
+        mfma_f4 *red = reinterpret_cast<mfma_f4 *>(col_lds);  // [NW][HB][64]
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            __syncthreads();  // the staging area, or the previous half, is done with
+#pragma unroll
+            for (int q = 0; q < HB; ++q) red[(wave * HB + q) * 64 + lane] = acc[h * HB + q];
+            __syncthreads();
+            for (int q = wave; q < HB; q += NW) {
+                mfma_f4 sum = red[q * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sum += red[(w * HB + q) * 64 + lane];
+                store_block(h * HB + q, sum);
+            }
+        }
+    }
+}
+
+template <int NJ, bool TAB, int NW>
+__global__ __launch_bounds__(64 * NW) void k_grid_cols(GridArgs a) {
+    grid_cols_body<NJ, TAB, NW>(a, blockIdx.x, blockIdx.y);
+}
+
+template <int NJ, bool TAB, int NW>
+__global__ __launch_bounds__(64 * NW) void k_grid_cols_multi(const GridArgs *__restrict__ jobs,
+                                                        const int4 *__restrict__ blocks) {
+    const int4 b = blocks[blockIdx.x];
+    grid_cols_body<NJ, TAB, NW>(jobs[b.x], b.y, b.z);
+}
+
 // V^H on the matrix cores in 3D, by blocks.  The tile is T0 x T1 x 16 (T0,
 // T1 in {8, 16}, at most 8 blocks); its leading axes are cut into 4 x 4
 // blocks, and a block with the 16 cells of the last axis is one 16 x 16
@@ -967,8 +1177,46 @@ hipError_t launch_grid_blk(const GridArgs &a, const GridArgs *jobs, const int4 *
     return launch_grid_blk_j<16, MULTI>(a, jobs, blocks, nblocks, lds, s);
 }
 
+template <int NJ, bool TAB, int NW>
+void launch_grid_cols_w(const GridArgs &a, const GridArgs *jobs, const int4 *blocks, int64_t nblocks, size_t lds,
+                        hipStream_t s) {
+    const dim3 block(64 * NW);
+    if (jobs)
+        launch_kernel((k_grid_cols_multi<NJ, TAB, NW>), dim3(unsigned(nblocks)), block, lds, s, jobs, blocks);
+    else
+        launch_kernel((k_grid_cols<NJ, TAB, NW>), dim3(unsigned(a.n_items), unsigned(grid_groups(a))), block, lds, s, a);
+}
+
+template <int NJ, bool TAB>
+void launch_grid_cols_t(const GridArgs &a, const GridArgs *jobs, const int4 *blocks, int64_t nblocks, size_t lds,
+                        hipStream_t s) {
+    if (a.cols == 4)
+        launch_grid_cols_w<NJ, TAB, 4>(a, jobs, blocks, nblocks, lds, s);
+    else
+        launch_grid_cols_w<NJ, TAB, 1>(a, jobs, blocks, nblocks, lds, s);
+}
+
+// One problem's launch, or (jobs != nullptr) a multi-problem one like a.
+hipError_t launch_grid_cols(const GridArgs &a, const GridArgs *jobs, const int4 *blocks, int64_t nblocks, size_t lds,
+                            hipStream_t s) {
+    if (a.geo.d != 2 || a.T[0] != 16 || a.T[1] != 16) return hipErrorInvalidValue;
+    const bool tab = use_table(a.geo);
+    if (a.geo.J <= 6 && tab)
+        launch_grid_cols_t<6, true>(a, jobs, blocks, nblocks, lds, s);
+    else if (a.geo.J <= 6)
+        launch_grid_cols_t<6, false>(a, jobs, blocks, nblocks, lds, s);
+    else if (a.geo.J <= 8 && tab)
+        launch_grid_cols_t<8, true>(a, jobs, blocks, nblocks, lds, s);
+    else if (a.geo.J <= 8)
+        launch_grid_cols_t<8, false>(a, jobs, blocks, nblocks, lds, s);
+    else
+        launch_grid_cols_t<16, false>(a, jobs, blocks, nblocks, lds, s);
+    return hipGetLastError();
+}
+
 hipError_t launch_grid(const GridArgs &a, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
+    if (a.cols) return launch_grid_cols(a, nullptr, nullptr, 0, grid_lds(a), s);
     if (a.blk) return launch_grid_blk<false>(a, nullptr, nullptr, 0, grid_lds(a), s);
     if (a.mfma) {
         switch (a.geo.d) {
@@ -989,6 +1237,10 @@ hipError_t launch_grid(const GridArgs &a, hipStream_t s) {
 // 6/8/16, row blocks) or vector ALUs (d, segment length, coefficient row
 // width), as launch_grid picks it; -1 if there is none.
 int grid_variant(const GridArgs &a) {
+    if (a.cols) {
+        if (a.geo.d != 2 || a.T[0] != 16 || a.T[1] != 16) return -1;
+        return 5000 + 100 * a.cols + 10 * (a.geo.J <= 6 ? 0 : a.geo.J <= 8 ? 1 : 2) + (use_table(a.geo) ? 1 : 0);
+    }
     if (a.blk) {
         if (a.geo.d != 3 || a.T[2] != 16 || (a.T[0] != 8 && a.T[0] != 16) || (a.T[1] != 8 && a.T[1] != 16) ||
             a.T[0] * a.T[1] > 128)
@@ -1011,7 +1263,13 @@ int grid_variant(const GridArgs &a) {
     return 2000 + 100 * a.geo.d + a.seg_len * 2 + (a.geo.jp == 16 ? 1 : 0);
 }
 
+int grid_groups(const GridArgs &a) {
+    const int gp = a.cols ? kColGrids : a.mfma ? a.grids_per_wg : 1;
+    return (a.grids + gp - 1) / gp;
+}
+
 size_t grid_lds(const GridArgs &a) {
+    if (a.cols) return size_t(64) * a.cols * ((2 * 16 + 1) + (2 * kColGrids + 1) + 1) * sizeof(float);
     if (a.blk) {
         const size_t staged = size_t(64) * a.grid_waves * (3 + a.T[0] + a.T[1] + a.T[2] + 1) * sizeof(float);
         return a.grid_waves == 1 ? staged : std::max(staged, size_t(a.grid_waves) * a.tile_cells * sizeof(float2));
@@ -1099,6 +1357,7 @@ hipError_t launch_grid_multi(const GridArgs *jobs, const int4 *blocks, int64_t n
                              size_t lds, hipStream_t s) {
     if (nblocks == 0) return hipSuccess;
     if (grid_variant(proto) < 0) return hipErrorInvalidValue;
+    if (proto.cols) return launch_grid_cols(proto, jobs, blocks, nblocks, lds, s);
     if (proto.blk) return launch_grid_blk<true>(proto, jobs, blocks, nblocks, lds, s);
     if (proto.mfma) {
         switch (proto.geo.d) {

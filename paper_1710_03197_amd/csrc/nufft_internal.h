@@ -273,9 +273,32 @@ struct GridArgs {
     int mfma;             // matrix-core gridding (d >= 2, T_last = 16, 16, 32 or 64 rows)
     int rec_stride;       // its LDS floats per staged sample: 2 + sum of T_a, made odd
     int blk;              // 3D matrix-core gridding by 4 x 4 blocks (T_2 = 16, T_0 and T_1 in {8, 16})
+    int cols;             // 2D matrix-core gridding with the grids as columns (16 x 16 tiles): its wavefronts
+                          // per work item (1 or 4), 0: not this form
     int grids_per_wg;     // row-tile matrix-core gridding: grids one workgroup grids together (1, 2, 4)
     int grid_waves;       // block gridding: wavefronts per work item (1 or 4)
 };
+// Wavefronts per work item of the column form, 0 where the row-tile form is
+// taken.  A product costs the same for one to eight grids, the row-tile form two
+// products per grid: it pays from three grids.  Calls of few samples stay with
+// the row-tile form: both are launch and latency bound there.  One wavefront
+// needs about 5 us for 64 samples, most of it LDS latency, so four share an item
+// (8 grids of 640 x 640: 92 us with one, 38 with four) until the items alone
+// fill the chip, as in a multi-problem launch (24 problems: 627 us with four,
+// 447 with one).  One wavefront adds all of an item's samples in one chain, so
+// it is kept to chunks whose rounding then stays at the row-tile form's (adjoint
+// error against float64 1.4e-7 at 1536 samples a chunk, 1.2e-7 at 512 and for
+// the row-tile form).
+constexpr int kColGrids = 8;  // grids that fill a product's 16 columns
+constexpr int kGridColsMin = 3;
+constexpr int64_t kGridColsWork = 32768;
+constexpr int64_t kGridColsItems = 12288;  // 12 wavefronts a CU, four deep
+constexpr int kGridColsChain = 512;        // samples one wavefront may sum in a chain
+inline int grid_cols_waves(int64_t items, int64_t M, int grids, int chunk, bool multi) {
+    if (grids < kGridColsMin || M * grids < kGridColsWork) return 0;
+    const bool filled = multi || items * ((grids + kColGrids - 1) / kColGrids) >= kGridColsItems;
+    return filled && chunk <= kGridColsChain ? 1 : 4;
+}
 // Grids per workgroup of the row-tile matrix-core gridding: the window weights
 // are staged once for all of them (coils and batch entries share the
 // trajectory); four at most, at most eight accumulator blocks per lane, and
@@ -474,6 +497,8 @@ hipError_t launch_interp_multi(const InterpArgs *jobs, const int4 *blocks, int64
 // share a launch) and its LDS bytes.
 int grid_variant(const GridArgs &a);
 size_t grid_lds(const GridArgs &a);
+// Groups of grids a gridding launch deals over gridDim.y.
+int grid_groups(const GridArgs &a);
 hipError_t launch_grid_multi(const GridArgs *jobs, const int4 *blocks, int64_t nblocks, const GridArgs &proto,
                              size_t lds, hipStream_t s);
 hipError_t launch_reduce_partials_multi(const ReduceArgs *jobs, const int4 *blocks, int64_t nblocks, hipStream_t s);
