@@ -332,7 +332,8 @@ int nufft_toeplitz_destroy(nufft_toeplitz_t t);
  * are ignored (the weights belong to the trajectory).  w_dev: device float
  * [M] in the caller's sample order, the starting weights on entry (e.g. all
  * 1) and the result on return.  The gridding reconstruction is then
- * x = A^H (y . w).  Allocates temporary buffers; synchronous on `stream`. */
+ * x = A^H (y . w).  The first call of a plan allocates two complex [M] buffers
+ * that the plan keeps; synchronous on `stream`. */
 int nufft_density_compensation(nufft_plan_t plan, int iters, float *w_dev, void *stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph

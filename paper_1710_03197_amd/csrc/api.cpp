@@ -177,6 +177,7 @@ struct nufft_plan_s {
     float2 *tmp = nullptr;
     float2 *partials = nullptr;
     float2 *ysorted = nullptr;  // [cap_grids][M] samples in sorted order for the gridding
+    float2 *dc = nullptr;       // [2][M] sample buffers of the density compensation, from its first call on
     hipStream_t last_stream = nullptr;
     // optional per-kernel event timing
     bool timing = false;
@@ -298,6 +299,7 @@ void free_plan(nufft_plan_s *p) {
     dfree(p->tmp);
     dfree(p->partials);
     dfree(p->ysorted);
+    dfree(p->dc);
 }
 
 // Tile edge on one axis: the largest divisor of K that is <= target, raised
@@ -742,11 +744,13 @@ int run_shfh(nufft_plan_s *p, const FftGeom &f, const float2 *h, int B, float2 *
     return NUFFT_OK;
 }
 
-int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s, Collector *col = nullptr) {
+// sorted: the samples are left in the plan's sorted order.
+int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s, Collector *col = nullptr,
+          bool sorted = false) {
     InterpArgs a{};
     a.geo = p->geom();
     a.om_sorted = p->om_sorted;
-    a.perm = p->perm;
+    a.perm = sorted ? p->biota : p->perm;
     a.M = p->M;
     a.G = G;
     a.grid_elems = p->grid_elems;
@@ -770,10 +774,12 @@ int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s,
 }
 
 // reduce = false leaves split tiles as partial tiles for the first inverse FFT
-// pass to sum (d >= 2 adjoint); stage_vh and 1D reduce here.
+// pass to sum (d >= 2 adjoint); stage_vh and 1D reduce here.  sorted: y is in
+// the plan's sorted order already.
 int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s, bool reduce = true,
-           Collector *col = nullptr) {
-    if (p->presort) {
+           Collector *col = nullptr, bool sorted = false) {
+    const bool permute = p->presort && !sorted;
+    if (permute) {
         if (col)
             col->add(kSlotPermute, kStPermute).permute = PermuteJob{y, p->perm, p->M, grids, p->ysorted};
         else
@@ -800,8 +806,8 @@ int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s
     a.chunk = p->chunk;
     a.items = p->items;
     a.n_items = p->n_items;
-    a.y = p->presort ? p->ysorted : y;
-    a.y_sorted = p->presort;
+    a.y = permute ? p->ysorted : y;
+    a.y_sorted = permute || sorted;
     a.grids = grids;
     a.h = h;
     a.n_kinds = segment_kinds(p->d, p->R, a.kinds);
@@ -2053,7 +2059,7 @@ int nufft_toeplitz_destroy(nufft_toeplitz_t t) {
 namespace {
 
 // `iters` density-compensation steps with the caller's buffers wc and u
-// (complex [M] each); asynchronous on s.
+// (complex [M] each, in the plan's sorted order); asynchronous on s.
 int dc_iterate(nufft_plan_s *plan, int iters, float *w_dev, float2 *wc, float2 *u, hipStream_t s) {
     // u = V V^H w with the kernel normalised to peak 1: gridding of w / c onto
     // the oversampled grid, interpolation, and a division by c again
@@ -2061,13 +2067,13 @@ int dc_iterate(nufft_plan_s *plan, int iters, float *w_dev, float2 *wc, float2 *
     for (int a = 0; a < plan->d; ++a) c *= kb_i0(plan->ker[a].beta);
     const float inv_c = float(1.0 / c);
     hipError_t e;
-    if ((e = launch_real_to_complex(w_dev, wc, plan->M, inv_c, s)) != hipSuccess)
+    if ((e = launch_weights_to_samples(w_dev, plan->perm, wc, plan->M, inv_c, s)) != hipSuccess)
         return hip_fail(e, "weights to samples");
     for (int it = 0; it < iters; ++it) {
         int st;
-        if ((st = run_vh(plan, wc, 1, plan->grid, s, true))) return st;
-        if ((st = run_v(plan, plan->grid, 1, u, s))) return st;
-        if ((e = launch_dc_update(w_dev, u, wc, plan->M, inv_c, s)) != hipSuccess)
+        if ((st = run_vh(plan, wc, 1, plan->grid, s, true, nullptr, true))) return st;
+        if ((st = run_v(plan, plan->grid, 1, u, s, nullptr, true))) return st;
+        if ((e = launch_dc_update(w_dev, plan->perm, u, wc, plan->M, inv_c, s)) != hipSuccess)
             return hip_fail(e, "density update");
     }
     return NUFFT_OK;
@@ -2092,17 +2098,13 @@ int nufft_density_compensation(nufft_plan_t plan, int iters, float *w_dev, void 
     if (plan->M == 0 || iters == 0) return NUFFT_OK;
     if ((st = ensure_workspace(plan, 1))) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    float2 *wc = nullptr, *u = nullptr;
+    // (two hipMalloc and hipFree a call took 100 of its 740 us at 6 iterations
+    // over 262144 samples)
+    if (!plan->dc)
+        HIP_TRY(dmalloc(&plan->dc, size_t(2) * size_t(plan->M)), "allocate density-compensation buffers");
+    st = dc_iterate(plan, iters, w_dev, plan->dc, plan->dc + plan->M, s);
     hipError_t e;
-    if ((e = dmalloc(&wc, size_t(plan->M))) != hipSuccess || (e = dmalloc(&u, size_t(plan->M))) != hipSuccess) {
-        dfree(wc);
-        dfree(u);
-        return hip_fail(e, "allocate density-compensation buffers");
-    }
-    st = dc_iterate(plan, iters, w_dev, wc, u, s);
     if ((e = hipStreamSynchronize(s)) != hipSuccess && !st) st = hip_fail(e, "density compensation");
-    dfree(wc);
-    dfree(u);
     return st;
 }
 

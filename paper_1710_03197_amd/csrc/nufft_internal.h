@@ -510,8 +510,10 @@ hipError_t launch_tv_rhs(int d, const int64_t *N, float mu, const float2 *ahy, c
 hipError_t launch_tv_normal(int d, const int64_t *N, float mu, const float2 *ahax, float lam, const float2 *x,
                             float2 *out, hipStream_t s);
 hipError_t launch_bregman_shrink(int64_t n, const float2 *r, float2 *dv, float2 *bv, float t, hipStream_t s);
-hipError_t launch_dc_update(float *w, const float2 *u, float2 *wc, int64_t M, float inv_c, hipStream_t s);
-hipError_t launch_real_to_complex(const float *w, float2 *wc, int64_t M, float scale, hipStream_t s);
+// wc, u: the plan's sorted sample order; w: the caller's.
+hipError_t launch_dc_update(float *w, const int *perm, const float2 *u, float2 *wc, int64_t M, float inv_c, hipStream_t s);
+hipError_t launch_weights_to_samples(const float *w, const int *perm, float2 *wc, int64_t M, float scale,
+                                     hipStream_t s);
 // The allocation-free density compensation's buffers: wc and u, kDcScratchMaxM
 // complex samples each, in a static device array of the current device.
 constexpr int64_t kDcScratchMaxM = int64_t(1) << 21;

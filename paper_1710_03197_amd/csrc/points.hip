@@ -102,20 +102,25 @@ __global__ void k_permute_points(const float *om, const int *perm, int64_t M, in
 // |u| * inv_c is the normalised V V^H w;  w[m] <- w[m] / (|u[m]| * inv_c)
 // (a zero or non-finite quotient keeps w[m]), and wc is refreshed for the
 // next gridding.  The 1/c pre-scaling keeps the grid values near the
-// weights' own scale (c^2d overflows float32 for d = 3 and J >= 8).
-__global__ __launch_bounds__(256) void k_dc_update(float *w, const float2 *u, float2 *wc, int64_t M, float inv_c) {
-    const int64_t m = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (m >= M) return;
-    const float a = hypotf(u[m].x, u[m].y) * inv_c;
+// weights' own scale (c^2d overflows float32 for d = 3 and J >= 8).  u and wc
+// are in the plan's sorted order, which the gridding reads and the gather
+// writes without a permutation; only the weights go through it.
+__global__ __launch_bounds__(256) void k_dc_update(float *w, const int *perm, const float2 *u, float2 *wc, int64_t M,
+                                                   float inv_c) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= M) return;
+    const int m = perm[i];
+    const float a = hypotf(u[i].x, u[i].y) * inv_c;
     float v = w[m];
     if (a > 0.f && isfinite(a)) v = v / a;
     w[m] = v;
-    wc[m] = make_float2(v * inv_c, 0.f);
+    wc[i] = make_float2(v * inv_c, 0.f);
 }
 
-__global__ __launch_bounds__(256) void k_real_to_complex(const float *w, float2 *wc, int64_t M, float scale) {
-    const int64_t m = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (m < M) wc[m] = make_float2(w[m] * scale, 0.f);
+__global__ __launch_bounds__(256) void k_weights_to_samples(const float *w, const int *perm, float2 *wc, int64_t M,
+                                                            float scale) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i < M) wc[i] = make_float2(w[perm[i]] * scale, 0.f);
 }
 
 // ------------------------------------------------------------ TV split-Bregman pieces
@@ -217,9 +222,9 @@ hipError_t launch_bin_keys(const BinArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_dc_update(float *w, const float2 *u, float2 *wc, int64_t M, float inv_c, hipStream_t s) {
+hipError_t launch_dc_update(float *w, const int *perm, const float2 *u, float2 *wc, int64_t M, float inv_c, hipStream_t s) {
     if (M == 0) return hipSuccess;
-    launch_kernel(k_dc_update, dim3(unsigned((M + 255) / 256)), dim3(256), 0, s, w, u, wc, M, inv_c);
+    launch_kernel(k_dc_update, dim3(unsigned((M + 255) / 256)), dim3(256), 0, s, w, perm, u, wc, M, inv_c);
     return hipGetLastError();
 }
 
@@ -245,9 +250,10 @@ hipError_t launch_weight_table(const SampleGeom &g, const float *om_sorted, int6
     }
 }
 
-hipError_t launch_real_to_complex(const float *w, float2 *wc, int64_t M, float scale, hipStream_t s) {
+hipError_t launch_weights_to_samples(const float *w, const int *perm, float2 *wc, int64_t M, float scale,
+                                     hipStream_t s) {
     if (M == 0) return hipSuccess;
-    launch_kernel(k_real_to_complex, dim3(unsigned((M + 255) / 256)), dim3(256), 0, s, w, wc, M, scale);
+    launch_kernel(k_weights_to_samples, dim3(unsigned((M + 255) / 256)), dim3(256), 0, s, w, perm, wc, M, scale);
     return hipGetLastError();
 }
 
