@@ -76,22 +76,6 @@ hipError_t upload(T **p, const std::vector<T> &v) {
     return hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
 }
 
-// Copy v into *p, reusing the buffer when it holds v (capacity *cap in
-// elements, grown, never shrunk): re-binning a trajectory of the same size
-// then allocates nothing.
-template <class T>
-hipError_t upload_into(T **p, size_t *cap, const std::vector<T> &v) {
-    if (v.size() > *cap || !*p) {
-        dfree(*p);
-        *cap = 0;
-        hipError_t e = dmalloc(p, std::max<size_t>(v.size(), 1));
-        if (e != hipSuccess) return e;
-        *cap = std::max<size_t>(v.size(), 1);
-    }
-    if (v.empty()) return hipSuccess;
-    return hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
-}
-
 bool smooth235(int64_t k) {
     for (int p : {2, 3, 5})
         while (k % p == 0) k /= p;
@@ -132,10 +116,12 @@ struct nufft_plan_s {
     float *om = nullptr;
     float *om_sorted = nullptr;
     int *perm = nullptr;
-    int *sub_start = nullptr;  // [nbins * 2^d + 1]
+    // work lists, all inside `tables` (grown, never shrunk)
+    char *tables = nullptr;
+    size_t cap_tables = 0;
     GridItem *items = nullptr;
     int64_t n_items = 0;
-    InterpItem *iitems = nullptr;  // nullptr: the gather reads the grid directly
+    InterpItem *iitems = nullptr;
     int64_t n_iitems = 0;
     bool staged_interp = true;
     int interp_merge = 1;  // tiles along the last axis one gather item may cover
@@ -151,13 +137,11 @@ struct nufft_plan_s {
     int stage_floats = 0;
     HotTile *hot = nullptr;
     int2 *split_of_tile = nullptr;  // [nbins]: (first partial slot, chunks), chunks 0 if not split
-    int2 *item_segs = nullptr;      // [n_items][kMaxNeighbors + 1]: (segment start, offset in the item's list)
+    int2 *item_segs = nullptr;      // [n_items][segments + 1]: (segment start, offset in the item's list)
     int64_t n_hot = 0;
     int64_t n_slots = 0;
-    // capacities of the binning tables above (elements; grown, never shrunk)
-    size_t cap_sub_start = 0, cap_items = 0, cap_iitems = 0, cap_hot = 0, cap_split = 0, cap_item_segs = 0;
     // binning scratch, sized at plan creation, so re-binning allocates nothing
-    int *bkeys = nullptr, *bkeys_sorted = nullptr, *biota = nullptr, *bcounts = nullptr, *bflag = nullptr;
+    int *bkeys = nullptr, *bkeys_sorted = nullptr, *biota = nullptr, *bcounts = nullptr;
     void *sort_temp = nullptr;
     size_t sort_temp_bytes = 0;
     float *om_prev = nullptr;  // the trajectory in force while a new one is binned
@@ -280,7 +264,6 @@ void free_plan(nufft_plan_s *p) {
     dfree(p->bkeys_sorted);
     dfree(p->biota);
     dfree(p->bcounts);
-    dfree(p->bflag);
     if (p->sort_temp) (void)hipFree(p->sort_temp);
     p->sort_temp = nullptr;
     dfree(p->om_prev);
@@ -288,12 +271,7 @@ void free_plan(nufft_plan_s *p) {
     dfree(p->om);
     dfree(p->om_sorted);
     dfree(p->perm);
-    dfree(p->sub_start);
-    dfree(p->items);
-    dfree(p->iitems);
-    dfree(p->hot);
-    dfree(p->split_of_tile);
-    dfree(p->item_segs);
+    dfree(p->tables);
     dfree(p->coils);
     dfree(p->grid);
     dfree(p->tmp);
@@ -324,20 +302,19 @@ int bits_for(int64_t n) {
 }
 
 // Bin the trajectory om (device, caller order) into the plan: sorted copy,
-// permutation, sub-bin offsets, gather and gridding work items.  Synchronous.
+// permutation, gather and gridding work items.  Synchronous.  The host waits
+// once, for the sub-bin counts, and makes the work lists while the GPU sorts;
+// all lists go up in one copy.
 int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
     const int64_t M = p->M;
     const int d = p->d;
     const int64_t nkeys = p->nbins << d;
     if (M > 0) HIP_TRY(hipMemcpyAsync(p->om, om_dev, size_t(M) * d * sizeof(float), hipMemcpyDeviceToDevice, s),
                        "copy trajectory");
-    int *keys = p->bkeys, *keys_sorted = p->bkeys_sorted, *iota = p->biota, *counts = p->bcounts, *flag = p->bflag;
-    std::vector<int> hcounts(size_t(nkeys), 0);
-    int hflag = 0;
+    std::vector<int> hcounts(size_t(nkeys) + 1, 0);  // the counts, then the flag
     hipError_t e = hipSuccess;
     do {
-        if ((e = hipMemsetAsync(counts, 0, size_t(nkeys) * sizeof(int), s)) != hipSuccess) break;
-        if ((e = hipMemsetAsync(flag, 0, sizeof(int), s)) != hipSuccess) break;
+        if ((e = hipMemsetAsync(p->bcounts, 0, size_t(nkeys + 1) * sizeof(int), s)) != hipSuccess) break;
         BinArgs ba{};
         ba.om = p->om;
         ba.M = M;
@@ -349,19 +326,18 @@ int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
             ba.T[a] = p->T[a];
             ba.nt[a] = p->nt[a];
         }
-        ba.keys = keys;
-        ba.counts = counts;
-        ba.flag = flag;
+        ba.keys = p->bkeys;
+        ba.counts = p->bcounts;
+        ba.flag = p->bcounts + nkeys;
         if ((e = launch_bin_keys(ba, s)) != hipSuccess) break;
-        if ((e = hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess) break;
-        if ((e = hipMemcpyAsync(hcounts.data(), counts, size_t(nkeys) * sizeof(int), hipMemcpyDeviceToHost, s)) !=
+        if ((e = hipMemcpyAsync(hcounts.data(), p->bcounts, hcounts.size() * sizeof(int), hipMemcpyDeviceToHost, s)) !=
             hipSuccess)
             break;
         if ((e = hipStreamSynchronize(s)) != hipSuccess) break;
-        if (hflag) break;
-        if ((e = launch_iota(iota, M, s)) != hipSuccess) break;
-        if ((e = sort_pairs(keys, keys_sorted, iota, p->perm, M, bits_for(nkeys), p->sort_temp, p->sort_temp_bytes,
-                            s)) != hipSuccess)
+        if (hcounts[size_t(nkeys)]) break;
+        if ((e = launch_iota(p->biota, M, s)) != hipSuccess) break;
+        if ((e = sort_pairs(p->bkeys, p->bkeys_sorted, p->biota, p->perm, M, bits_for(nkeys), p->sort_temp,
+                            p->sort_temp_bytes, s)) != hipSuccess)
             break;
         if ((e = launch_permute_points(p->om, p->perm, M, d, p->om_sorted, s)) != hipSuccess) break;
         if (p->use_wtab) {
@@ -376,45 +352,47 @@ int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
             }
             if ((e = launch_weight_table(p->geom(), p->om_sorted, M, p->wtab, s)) != hipSuccess) break;
         }
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) break;
     } while (false);
     if (e != hipSuccess) return hip_fail(e, "binning the trajectory");
-    if (hflag) return fail(NUFFT_ERR_NONFINITE, "trajectory has a NaN, infinite or out-of-range coordinate");
+    if (hcounts[size_t(nkeys)])
+        return fail(NUFFT_ERR_NONFINITE, "trajectory has a NaN, infinite or out-of-range coordinate");
 
     // sub-bin offsets: sorted order is (tile, crossing code), stable in the caller's order
     std::vector<int> start(size_t(nkeys) + 1, 0);
     for (int64_t k = 0; k < nkeys; ++k) start[k + 1] = start[k] + hcounts[k];
-    // gridding work items: per tile, the samples whose windows reach it, in chunks
-    std::vector<GridItem> items;
-    std::vector<HotTile> hot;
-    std::vector<InterpItem> iitems;
-    int64_t slots = 0;
-    items.reserve(size_t(p->nbins));
-    const int ichunk = 256 * kInterpSamplesPerThread;
-    for (int64_t t = 0; t < p->nbins; ++t) {
-        int tc[kMaxDim];
-        int64_t rem = t;
-        for (int a = d - 1; a >= 0; --a) {
-            tc[a] = int(rem % p->nt[a]);
-            rem /= p->nt[a];
-        }
-        int lo[kMaxNeighbors], hi[kMaxNeighbors];
-        const int nseg = tile_segments(d, tc, p->nt, p->R, start.data(), lo, hi);
-        int64_t S = 0;
-        for (int q = 0; q < nseg; ++q) S += hi[q] - lo[q];
-        const int nch = int(std::max<int64_t>(1, (S + p->chunk - 1) / p->chunk));
-        const int slot = nch > 1 ? int(slots) : -1;
-        for (int c = 0; c < nch; ++c) items.push_back(GridItem{int(t), c, nch, slot});
-        if (nch > 1) {
-            hot.push_back(HotTile{int(t), slot, nch, 0});
-            slots += nch;
+    // Per tile the segments of sorted samples whose windows reach it, in the
+    // order tile_segments lists them: (first sorted sample, offset of the
+    // segment in the tile's sample list), and (0, total) after the last.
+    int kinds[kMaxNeighbors];
+    const int nseg = segment_kinds(d, p->R, kinds);
+    const size_t row = size_t(nseg) + 1;
+    std::vector<int2> tile_segs(size_t(p->nbins) * row);
+    int64_t n_items = 0, n_hot = 0, slots = 0;
+    {
+        int tc[kMaxDim] = {0, 0, 0};
+        for (int64_t t = 0; t < p->nbins; ++t) {
+            int lo[kMaxNeighbors], hi[kMaxNeighbors];
+            tile_segments(d, tc, p->nt, p->R, start.data(), lo, hi);
+            int2 *seg = &tile_segs[size_t(t) * row];
+            int pre = 0;
+            for (int k = 0; k < nseg; ++k) {
+                seg[k] = make_int2(lo[k], pre);
+                pre += hi[k] - lo[k];
+            }
+            seg[nseg] = make_int2(0, pre);
+            const int nch = std::max(1, int((int64_t(pre) + p->chunk - 1) / p->chunk));
+            n_items += nch;
+            n_hot += nch > 1;
+            for (int a = d - 1; a >= 0 && ++tc[a] == p->nt[a]; --a) tc[a] = 0;
         }
     }
     // Gather work items: a crowded tile's own bin in chunks of `ichunk`; runs
     // of sparse tiles along the last axis (their samples are contiguous in the
     // sorted order) share one item of at most `ichunk` samples and
     // interp_merge tiles, which stages one region for all of them.
-    {
+    const int ichunk = 256 * kInterpSamplesPerThread;
+    std::vector<InterpItem> iitems;
+    if (p->staged_interp) {
         const int nt_last = p->nt[d - 1];
         int64_t t = 0;
         while (t < p->nbins) {
@@ -437,76 +415,93 @@ int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
             t = u;
         }
     }
+    // One buffer of all lists: split-tile index, hot tiles, gridding items and
+    // their segment rows, gather items.
+    auto place = [](size_t &off, size_t bytes) {
+        const size_t at = off;
+        off = (off + bytes + 255) & ~size_t(255);
+        return at;
+    };
+    size_t total = 0;
+    const size_t at_split = place(total, size_t(p->nbins) * sizeof(int2));
+    const size_t at_hot = place(total, size_t(n_hot) * sizeof(HotTile));
+    const size_t at_items = place(total, size_t(n_items) * sizeof(GridItem));
+    const size_t at_segs = place(total, size_t(n_items) * row * sizeof(int2));
+    const size_t at_iitems = place(total, iitems.size() * sizeof(InterpItem));
+    std::vector<char> host(std::max<size_t>(total, 1));
+    int2 *split = reinterpret_cast<int2 *>(host.data() + at_split);
+    HotTile *hot = reinterpret_cast<HotTile *>(host.data() + at_hot);
+    GridItem *items = reinterpret_cast<GridItem *>(host.data() + at_items);
+    int2 *segs = reinterpret_cast<int2 *>(host.data() + at_segs);
     // Longest items first: workgroups are dealt to the XCDs round-robin in
     // launch order, so the crowded tiles (all at the k-space centre, i.e. at
     // the two ends of the tile order) spread over the whole chip and the
-    // light tiles fill in behind them.
+    // light tiles fill in behind them.  Counting sorts, stable, by size.
+    // (Measured: keeping gather items in tile order, dealt to the XCDs in
+    // runs of neighbouring tiles, cuts the 3D gather's HBM reads by a
+    // third through L2 hits on the halos but runs slower than longest
+    // first, which balances the crowded centre over the chip.)
+    auto by_size = [](std::vector<size_t> &at) {  // at[c]: items of size c -> first place, larger sizes first
+        size_t sum = 0;
+        for (size_t c = at.size(); c-- > 0;) {
+            const size_t n = at[c];
+            at[c] = sum;
+            sum += n;
+        }
+    };
     {
-        std::vector<int64_t> cnt(items.size());
-        std::vector<int> ord(items.size());
-        for (size_t q = 0; q < items.size(); ++q) {
-            const GridItem &gi = items[q];
-            int tc[kMaxDim];
-            int64_t rem = gi.tile;
-            for (int a = d - 1; a >= 0; --a) {
-                tc[a] = int(rem % p->nt[a]);
-                rem /= p->nt[a];
+        const int cap = int(std::min<int64_t>(p->chunk, std::max<int64_t>(M << d, 1)));  // largest size that occurs
+        std::vector<size_t> at(size_t(cap) + 1, 0);
+        auto size_of = [&](int64_t t, int c) {
+            const int64_t S = tile_segs[size_t(t) * row + size_t(nseg)].y;
+            return size_t(std::min<int64_t>(p->chunk, S - int64_t(c) * p->chunk));
+        };
+        auto chunks_of = [&](int64_t t) {
+            const int64_t S = tile_segs[size_t(t) * row + size_t(nseg)].y;
+            return int(std::max<int64_t>(1, (S + p->chunk - 1) / p->chunk));
+        };
+        for (int64_t t = 0; t < p->nbins; ++t)
+            for (int c = 0; c < chunks_of(t); ++c) ++at[size_of(t, c)];
+        by_size(at);
+        for (int64_t t = 0; t < p->nbins; ++t) {
+            const int nch = chunks_of(t);
+            const int slot = nch > 1 ? int(slots) : -1;
+            split[t] = nch > 1 ? make_int2(slot, nch) : make_int2(0, 0);
+            if (nch > 1) {
+                *hot++ = HotTile{int(t), slot, nch, 0};
+                slots += nch;
             }
-            int lo[kMaxNeighbors], hi[kMaxNeighbors];
-            const int nseg = tile_segments(d, tc, p->nt, p->R, start.data(), lo, hi);
-            int64_t S = 0;
-            for (int k = 0; k < nseg; ++k) S += hi[k] - lo[k];
-            cnt[q] = std::min<int64_t>(p->chunk, S - int64_t(gi.chunk) * p->chunk);
-            ord[q] = int(q);
+            for (int c = 0; c < nch; ++c) {
+                const size_t q = at[size_of(t, c)]++;
+                items[q] = GridItem{int(t), c, nch, slot};
+                std::copy_n(&tile_segs[size_t(t) * row], row, segs + q * row);
+            }
         }
-        std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return cnt[x] > cnt[y]; });
-        std::vector<GridItem> sorted(items.size());
-        for (size_t q = 0; q < ord.size(); ++q) sorted[q] = items[ord[q]];
-        items.swap(sorted);
-        // (Measured: keeping gather items in tile order, dealt to the XCDs in
-        // runs of neighbouring tiles, cuts the 3D gather's HBM reads by a
-        // third through L2 hits on the halos but runs slower than longest
-        // first, which balances the crowded centre over the chip.)
-        std::stable_sort(iitems.begin(), iitems.end(),
-                         [](const InterpItem &x, const InterpItem &y) { return x.count > y.count; });
+        std::vector<size_t> iat(size_t(ichunk) + 1, 0);
+        for (const InterpItem &it : iitems) ++iat[size_t(it.count)];
+        by_size(iat);
+        InterpItem *dst = reinterpret_cast<InterpItem *>(host.data() + at_iitems);
+        for (const InterpItem &it : iitems) dst[iat[size_t(it.count)]++] = it;
     }
-    std::vector<int2> split_of_tile(size_t(p->nbins), make_int2(0, 0));
-    for (const HotTile &h : hot) split_of_tile[size_t(h.tile)] = make_int2(h.slot, h.nchunks);
-    // The segments of every gridding item's tile, in the order tile_segments
-    // lists them: (first sorted sample, offset of the segment in the item's
-    // sample list), and (0, total) after the last, so a work item reads its
-    // table in the same round trip as the item itself.
-    constexpr int kSegRow = kMaxNeighbors + 1;
-    std::vector<int2> item_segs(std::max<size_t>(items.size(), 1) * kSegRow, make_int2(0, 0));
-    for (size_t q = 0; q < items.size(); ++q) {
-        int tc[kMaxDim];
-        int64_t rem = items[q].tile;
-        for (int a = d - 1; a >= 0; --a) {
-            tc[a] = int(rem % p->nt[a]);
-            rem /= p->nt[a];
-        }
-        int lo[kMaxNeighbors], hi[kMaxNeighbors];
-        const int nseg = tile_segments(d, tc, p->nt, p->R, start.data(), lo, hi);
-        int pre = 0;
-        for (int k = 0; k < nseg; ++k) {
-            item_segs[q * kSegRow + size_t(k)] = make_int2(lo[k], pre);
-            pre += hi[k] - lo[k];
-        }
-        item_segs[q * kSegRow + size_t(nseg)] = make_int2(0, pre);
+    if (total > p->cap_tables) {
+        HIP_TRY(hipStreamSynchronize(s), "binning the trajectory");
+        dfree(p->tables);
+        p->cap_tables = 0;
+        const size_t cap = total + total / 4;  // room for the next trajectory's lists
+        HIP_TRY(dmalloc(&p->tables, cap), "allocate work lists");
+        p->cap_tables = cap;
     }
-    HIP_TRY(upload_into(&p->sub_start, &p->cap_sub_start, start), "upload bin offsets");
-    HIP_TRY(upload_into(&p->item_segs, &p->cap_item_segs, item_segs), "upload gridding segment tables");
-    HIP_TRY(upload_into(&p->split_of_tile, &p->cap_split, split_of_tile), "upload split-tile index");
-    HIP_TRY(upload_into(&p->items, &p->cap_items, items), "upload gridding work items");
-    HIP_TRY(upload_into(&p->hot, &p->cap_hot, hot), "upload split tiles");
-    p->n_items = int64_t(items.size());
-    p->n_hot = int64_t(hot.size());
+    p->split_of_tile = reinterpret_cast<int2 *>(p->tables + at_split);
+    p->hot = reinterpret_cast<HotTile *>(p->tables + at_hot);
+    p->items = reinterpret_cast<GridItem *>(p->tables + at_items);
+    p->item_segs = reinterpret_cast<int2 *>(p->tables + at_segs);
+    p->iitems = reinterpret_cast<InterpItem *>(p->tables + at_iitems);
+    p->n_items = n_items;
+    p->n_hot = n_hot;
     p->n_slots = slots;
-    p->n_iitems = 0;
-    if (p->staged_interp) {
-        HIP_TRY(upload_into(&p->iitems, &p->cap_iitems, iitems), "upload gather work items");
-        p->n_iitems = int64_t(iitems.size());
-    }
+    p->n_iitems = int64_t(iitems.size());
+    HIP_TRY(hipMemcpyAsync(p->tables, host.data(), total, hipMemcpyHostToDevice, s), "upload work lists");
+    HIP_TRY(hipStreamSynchronize(s), "binning the trajectory");
     return NUFFT_OK;
 }
 
@@ -791,7 +786,6 @@ int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s
     a.geo = p->geom();
     a.om_sorted = p->om_sorted;
     a.perm = p->perm;
-    a.sub_start = p->sub_start;
     a.M = p->M;
     for (int ax = 0; ax < p->d; ++ax) {
         a.T[ax] = p->T[ax];
@@ -1676,13 +1670,12 @@ int nufft_plan_ex(int d, const int64_t *N, const int64_t *K, int J, int64_t M, c
             (e = dmalloc(&p->perm, size_t(std::max<int64_t>(M, 1)))) != hipSuccess ||
             (e = dmalloc(&p->om_prev, size_t(std::max<int64_t>(M, 1)) * d)) != hipSuccess)
             return bail(hip_fail(e, "allocate trajectory"));
-        // binning scratch: keys, sorted keys, identity, sub-bin counts, flag and
+        // binning scratch: keys, sorted keys, identity, sub-bin counts with a flag, and
         // the radix sort's temporary storage, kept for every later re-bin
         const size_t m1 = size_t(std::max<int64_t>(M, 1));
         if ((e = dmalloc(&p->bkeys, m1)) != hipSuccess || (e = dmalloc(&p->bkeys_sorted, m1)) != hipSuccess ||
             (e = dmalloc(&p->biota, m1)) != hipSuccess ||
-            (e = dmalloc(&p->bcounts, size_t(p->nbins << d))) != hipSuccess ||
-            (e = dmalloc(&p->bflag, 1)) != hipSuccess ||
+            (e = dmalloc(&p->bcounts, size_t(p->nbins << d) + 1)) != hipSuccess ||
             (e = sort_pairs_temp_bytes(M, bits_for(p->nbins << d), &p->sort_temp_bytes)) != hipSuccess ||
             (e = hipMalloc(&p->sort_temp, std::max<size_t>(p->sort_temp_bytes, 1))) != hipSuccess)
             return bail(hip_fail(e, "allocate binning scratch"));

@@ -59,9 +59,8 @@ __device__ __forceinline__ void group_sync(int gsize) {
 // nothing from the item record, so both loads are in flight together.  Every
 // thread of the workgroup calls it; returns the number of segments.
 __device__ __forceinline__ int grid_item_segments(const GridArgs &a, int64_t item, int *seg_lo, int *seg_pre) {
-    constexpr int kSegRow = kMaxNeighbors + 1;
     if (threadIdx.x <= a.n_kinds) {
-        const int2 e = a.item_segs[item * kSegRow + threadIdx.x];
+        const int2 e = a.item_segs[item * (a.n_kinds + 1) + threadIdx.x];
         seg_lo[threadIdx.x] = e.x;
         seg_pre[threadIdx.x] = e.y;
     }

@@ -245,7 +245,6 @@ struct GridArgs {
     SampleGeom geo;
     const float *om_sorted;
     const int *perm;
-    const int *sub_start;  // [nbins * 2^d + 1] offsets of the (bin, crossing code) sub-bins
     int64_t M;
     int T[kMaxDim];
     int nt[kMaxDim];
@@ -268,7 +267,7 @@ struct GridArgs {
     int64_t grid_elems;
     float2 *partials;     // [grids][n_slots][tile_cells]
     int64_t n_slots;
-    const int2 *item_segs;  // [n_items][kMaxNeighbors + 1]: per segment of the item's tile (first
+    const int2 *item_segs;  // [n_items][n_kinds + 1]: per segment of the item's tile (first
                             // sorted sample, offset in the item's list), then (0, total)
     int mfma;             // matrix-core gridding (d >= 2, T_last = 16, 16, 32 or 64 rows)
     int rec_stride;       // its LDS floats per staged sample: 2 + sum of T_a, made odd
@@ -441,7 +440,7 @@ struct BinArgs {
     int nt[kMaxDim];
     int *keys;
     int *counts;
-    int *flag;  // set to 1 on a non-finite coordinate
+    int *flag;  // set to 1 on a non-finite coordinate (zero at the start, as counts)
 };
 hipError_t launch_bin_keys(const BinArgs &a, hipStream_t s);
 hipError_t launch_iota(int *v, int64_t n, hipStream_t s);

@@ -34,8 +34,8 @@ __global__ __launch_bounds__(256) void k_weight_table(SampleGeom geo, const floa
 // key = (tile of the first tap) * 2^d + crossing code, bit a set when the
 // window leaves the tile through its upper face along axis a.
 __global__ __launch_bounds__(256) void k_bin_keys(BinArgs a) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= a.M) return;
+    const int64_t i0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t i = min(i0, a.M - 1);
     int key = 0, code = 0;
     bool bad = false;
     for (int ax = 0; ax < a.d; ++ax) {
@@ -59,8 +59,19 @@ __global__ __launch_bounds__(256) void k_bin_keys(BinArgs a) {
     }
     key = (key << a.d) | code;
     if (bad) atomicOr(a.flag, 1);
+    // Consecutive samples of a readout mostly share a sub-bin: one atomic per
+    // run of equal keys in the wavefront (the crowded centre serialises them).
+    // Lanes past the last sample end the last run.
+    const bool live = i0 < a.M;
+    const int lane = threadIdx.x & 63;
+    const int before = __shfl_up(key, 1);
+    const uint64_t heads = __ballot(!live || lane == 0 || key != before);
+    if (!live) return;
     a.keys[i] = key;
-    atomicAdd(&a.counts[key], 1);
+    if ((heads >> lane) & 1u) {
+        const uint64_t rest = lane == 63 ? 0 : heads >> (lane + 1);
+        atomicAdd(&a.counts[key], rest ? int(__builtin_ctzll(rest)) + 1 : 64 - lane);
+    }
 }
 
 __global__ void k_iota(int *v, int64_t n) {
