@@ -82,7 +82,9 @@ int nufft_plan(int d, const int64_t *N, const int64_t *K, int J, int64_t M,
 /* Tuning knobs of a plan; 0 in any field keeps the built-in default.  Any
  * choice gives the same operator (to float32 rounding); only speed changes.
  *   tile[a]       grid tile edge on axis a for binning, gathering and
- *                 gridding (rounded to a divisor of K_a that is >= J - 1)
+ *                 gridding (rounded to a divisor of K_a that is >= J - 1; the
+ *                 defaults need not divide K_a: tiles of at most that many
+ *                 cells, evenly cut)
  *   grid_chunk    samples per gridding work item (>= 64)
  *   fft_groups    workgroups the FFT passes aim to launch (sets lines or
  *                 columns per workgroup)

@@ -501,6 +501,25 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned n) {
     return x * q + min(x, r) + b / kXcds;
 }
 
+// tile_of and the cell within the tile (tile_base), by high multiplies: the
+// dividends stay below K nt <= 2^20 and the divisors below 2^12.
+struct TileMap {
+    bool even;  // tiles of T cells
+    int T, nt, half;
+    FastDiv byT, by_half, by_nt;
+    __device__ __forceinline__ TileMap(int K, int T_, int nt_)
+        : even(T_ * nt_ == K), T(T_), nt(nt_), half(K / 2), byT(T_), by_half(K / 2), by_nt(nt_) {}
+    __device__ __forceinline__ void find(int k, int &t, int &l) const {
+        if (even) {
+            t = byT.div(k);
+            l = byT.rem(k, t);
+        } else {
+            t = by_half.div(((k >> 1) + 1) * nt - 1);
+            l = k - 2 * by_nt.div(t * half);
+        }
+    }
+};
+
 // Forms of the inverse pass with instances of their own, so the plain passes
 // keep their register budget: the first inverse pass of an adjoint whose split
 // gridding tiles are still partial tiles, and the first inverse pass after a
@@ -537,23 +556,25 @@ __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int 
             // the bits, of k_reduce_partials).  Grid row q on axis 0, column
             // c0 + w over the remaining axes; the input and the cell's split
             // entry are loaded together, the partial tiles after that.
-            const FastDiv byT0(a.T[0]), byT1(a.T[1]), byT2(a.d > 2 ? a.T[2] : 1), byK2(a.d > 2 ? a.Kax[2] : 1);
+            const TileMap m0(a.Kax[0], a.T[0], a.nt[0]), m1(a.Kax[1], a.T[1], a.nt[1]);
+            const FastDiv byK2(a.d > 2 ? a.Kax[2] : 1);
             const int c = int(c0) + w;
-            int k1 = c, k2 = 0;
+            int k1 = c, t2 = 0, l2 = 0;
             if (a.d > 2) {
                 k1 = byK2.div(c);
-                k2 = byK2.rem(c, k1);
+                TileMap(a.Kax[2], a.T[2], a.nt[2]).find(byK2.rem(c, k1), t2, l2);
             }
-            const int t1 = byT1.div(k1), t2 = byT2.div(k2);
-            const int l1 = byT1.rem(k1, t1), l2 = byT2.rem(k2, t2);
+            int t1, l1;
+            m1.find(k1, t1, l1);
             int2 sp[R];
             int cell[R];
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const int q = j + u * nbl;
-                const int t0 = byT0.div(q);
+                int t0, l0;
+                m0.find(q, t0, l0);
                 int tile = t0 * a.nt[1] + t1;
-                cell[u] = byT0.rem(q, t0) * a.T[1] + l1;
+                cell[u] = l0 * a.T[1] + l1;
                 if (a.d > 2) {
                     tile = tile * a.nt[2] + t2;
                     cell[u] = cell[u] * a.T[2] + l2;

@@ -35,7 +35,7 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
     int rows = 1;
 #pragma unroll
     for (int ax = 0; ax < DIM; ++ax) {
-        base[ax] = tc[ax] * a.T[ax];
+        base[ax] = tile_base(tc[ax], a.geo.K[ax], a.T[ax], a.nt[ax]);
         // a run of it.tiles tiles along the last axis, plus the J - 1 halo
         E[ax] = (ax == DIM - 1 ? it.tiles : 1) * a.T[ax] + J - 1;
         if (ax < DIM - 1) rows *= E[ax];

@@ -347,12 +347,13 @@ __device__ __forceinline__ void grid_mfma_body(const GridArgs &a, int64_t item, 
     const int total = seg_pre[nseg];
     const int f0 = it.chunk * a.chunk;
     const int n = min(total, f0 + a.chunk) - f0;
-    int base[DIM], off[DIM];
+    int base[DIM], width[DIM], off[DIM];
     {
         int o = 2 * GP;
 #pragma unroll
         for (int ax = 0; ax < DIM; ++ax) {
-            base[ax] = tc[ax] * a.T[ax];
+            base[ax] = tile_base(tc[ax], a.geo.K[ax], a.T[ax], a.nt[ax]);
+            width[ax] = tile_base(tc[ax] + 1, a.geo.K[ax], a.T[ax], a.nt[ax]) - base[ax];
             off[ax] = o;
             o += a.T[ax];
         }
@@ -518,8 +519,13 @@ __device__ __forceinline__ void grid_mfma_body(const GridArgs &a, int64_t item, 
                         rr /= a.T[ax];
                     }
                     idx = 0;
+                    bool in = true;
 #pragma unroll
-                    for (int ax = 0; ax < DIM; ++ax) idx = idx * a.geo.K[ax] + base[ax] + l[ax];
+                    for (int ax = 0; ax < DIM; ++ax) {
+                        idx = idx * a.geo.K[ax] + base[ax] + l[ax];
+                        in = in && l[ax] < width[ax];
+                    }
+                    if (!in) continue;  // past the tile's own cells
                 }
                 dst[idx] = sum;
             }
@@ -571,7 +577,10 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     float *val = rec + 64 * RS;                                       // [64][VS]
     unsigned *smask = reinterpret_cast<unsigned *>(val + 64 * VS);    // [64]
     const int t0 = it.tile / a.nt[1];
-    const int base[2] = {t0 * T, (it.tile - t0 * a.nt[1]) * T};
+    const int t1 = it.tile - t0 * a.nt[1];
+    const int base[2] = {tile_base(t0, a.geo.K[0], T, a.nt[0]), tile_base(t1, a.geo.K[1], T, a.nt[1])};
+    const int width[2] = {tile_base(t0 + 1, a.geo.K[0], T, a.nt[0]) - base[0],
+                          tile_base(t1 + 1, a.geo.K[1], T, a.nt[1]) - base[1]};
     const int total = seg_pre[nseg];
     const int f0 = it.chunk * a.chunk;
     const int n = min(total, f0 + a.chunk) - f0;
@@ -708,8 +717,9 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     auto store_block = [&](int q, mfma_f4 v) {
         const float u0 = swap_lane(odd ? v[0] : v[2]), u1 = swap_lane(odd ? v[1] : v[3]);
         const float4 cells = odd ? make_float4(u0, v[2], u1, v[3]) : make_float4(v[0], u0, v[1], u1);
-        const int64_t idx = first + (4 * (q >> 2) + kq) * pitch + 4 * (q & 3) + (odd ? 2 : 0);
-        if (g - g0 < ng) *reinterpret_cast<float4 *>(dst + idx) = cells;
+        const int x0 = 4 * (q >> 2) + kq, x1 = 4 * (q & 3) + (odd ? 2 : 0);
+        const int64_t idx = first + x0 * pitch + x1;
+        if (g - g0 < ng && (to_partial || (x0 < width[0] && x1 < width[1]))) *reinterpret_cast<float4 *>(dst + idx) = cells;
     };
     if constexpr (NW == 1) {
 #pragma unroll
@@ -793,7 +803,8 @@ __device__ __forceinline__ void grid_blk_body(const GridArgs &a, int64_t item, i
             t /= a.nt[ax];
         }
     }
-    const int base[3] = {tc[0] * T0, tc[1] * T1, tc[2] * T2};
+    const int base[3] = {tile_base(tc[0], a.geo.K[0], T0, a.nt[0]), tile_base(tc[1], a.geo.K[1], T1, a.nt[1]),
+                         tile_base(tc[2], a.geo.K[2], T2, a.nt[2])};
     const int total = seg_pre[nseg];
     const int f0 = it.chunk * a.chunk;
     const int n = min(total, f0 + a.chunk) - f0;
@@ -944,6 +955,10 @@ __device__ __forceinline__ void grid_blk_body(const GridArgs &a, int64_t item, i
     float2 *dst = to_partial ? a.partials + (int64_t(g) * a.n_slots + it.slot + it.chunk) * a.tile_cells
                              : a.h + int64_t(g) * a.grid_elems;
     const int64_t K1 = a.geo.K[1], K2 = a.geo.K[2];
+    // the tile's own cells (partial tiles are stored whole)
+    const int w0 = to_partial ? T0 : tile_base(tc[0] + 1, a.geo.K[0], T0, a.nt[0]) - base[0];
+    const int w1 = to_partial ? T1 : tile_base(tc[1] + 1, a.geo.K[1], T1, a.nt[1]) - base[1];
+    const int w2 = to_partial ? T2 : tile_base(tc[2] + 1, a.geo.K[2], T2, a.nt[2]) - base[2];
     if constexpr (NW == 1) {
 #pragma unroll
         for (int q = 0; q < NBLK; ++q) {
@@ -953,7 +968,7 @@ __device__ __forceinline__ void grid_blk_body(const GridArgs &a, int64_t item, i
                 const int x1 = 4 * (q % NB1) + r;
                 const int64_t idx = to_partial ? int64_t((x0 * T1 + x1) * T2 + rl)
                                                : (int64_t(base[0] + x0) * K1 + base[1] + x1) * K2 + base[2] + rl;
-                dst[idx] = make_float2(acc_re[q][r], acc_im[q][r]);
+                if (x0 < w0 && x1 < w1 && rl < w2) dst[idx] = make_float2(acc_re[q][r], acc_im[q][r]);
             }
         }
         return;
@@ -977,7 +992,7 @@ __device__ __forceinline__ void grid_blk_body(const GridArgs &a, int64_t item, i
         for (int w = 1; w < NW; ++w) sum = cadd(sum, red[w * CELLS + e]);
         const int x2 = e % T2, x1 = (e / T2) % T1, x0 = e / (T1 * T2);
         const int64_t idx = to_partial ? int64_t(e) : (int64_t(base[0] + x0) * K1 + base[1] + x1) * K2 + base[2] + x2;
-        dst[idx] = sum;
+        if (x0 < w0 && x1 < w1 && x2 < w2) dst[idx] = sum;
     }
 }
 
@@ -1039,7 +1054,11 @@ __device__ __forceinline__ void reduce_partials_body(const ReduceArgs &a, int64_
         rem /= a.T[ax];
     }
     int64_t idx = 0;
-    for (int ax = 0; ax < a.d; ++ax) idx = idx * a.K[ax] + tc[ax] * a.T[ax] + l[ax];
+    for (int ax = 0; ax < a.d; ++ax) {
+        const int k = tile_base(tc[ax], a.K[ax], a.T[ax], a.nt[ax]) + l[ax];
+        if (k >= tile_base(tc[ax] + 1, a.K[ax], a.T[ax], a.nt[ax])) return;  // past the tile's own cells
+        idx = idx * a.K[ax] + k;
+    }
     a.h[int64_t(g) * a.grid_elems + idx] = acc;
 }
 

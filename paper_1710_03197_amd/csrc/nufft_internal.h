@@ -25,6 +25,17 @@ constexpr int kInterpSamplesPerThread = 2;  // gather work item = 512 samples
 constexpr int kLdsBudget = 64 * 1024;      // bytes of LDS a gather or gridding tile may use
 constexpr int kInterpLdsBudget = 64 * 1024;  // bytes of LDS a gather item covering several tiles may use
 
+// Grid tiles of an axis of K cells: nt tiles of T cells where T nt = K, else nt
+// tiles cut as evenly as even boundaries allow, at most T cells each (so a tile
+// shape the matrix-core gridding takes fits any K).  First cell of tile t (t =
+// nt: K), and the tile of cell k.
+__host__ __device__ inline int tile_base(int t, int K, int T, int nt) {
+    return T * nt == K ? t * T : 2 * int(unsigned(t) * unsigned(K / 2) / unsigned(nt));
+}
+__host__ __device__ inline int tile_of(int k, int K, int T, int nt) {
+    return T * nt == K ? k / T : int((unsigned(k / 2 + 1) * unsigned(nt) - 1u) / unsigned(K / 2));
+}
+
 // Radix schedule of one FFT axis (Stockham, product of r[] == K, n >= 2: a
 // length of one radix gets a pass of radix 1 after it).  Per pass p: ns = r[0]
 // ... r[p-1] the length of the sub-transforms done so far, nbl = K / r[p] its

@@ -51,8 +51,9 @@ __global__ __launch_bounds__(256) void k_bin_keys(BinArgs a) {
                 const double k0 = floor(u - 0.5 * a.J) + 1.0;
                 long long kw = static_cast<long long>(k0) % a.K[ax];
                 if (kw < 0) kw += a.K[ax];
-                tile = int(kw) / a.T[ax];
-                if (a.nt[ax] > 1 && int(kw) - tile * a.T[ax] + a.J - 1 >= a.T[ax]) code |= 1 << ax;
+                tile = tile_of(int(kw), a.K[ax], a.T[ax], a.nt[ax]);
+                if (a.nt[ax] > 1 && int(kw) + a.J - 1 >= tile_base(tile + 1, a.K[ax], a.T[ax], a.nt[ax]))
+                    code |= 1 << ax;
             }
         }
         key = key * a.nt[ax] + tile;
