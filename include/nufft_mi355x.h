@@ -120,8 +120,10 @@ int nufft_plan(int d, const int64_t *N, const int64_t *K, int J, int64_t M,
  *                 gridding and the staged interpolation read it instead of
  *                 evaluating the kernel per sample (the paper's precomputed
  *                 interpolator, Section 2.1 "Interpolation"); Kaiser-Bessel
- *                 only (with min-max: NUFFT_ERR_UNSUPPORTED); 0: evaluate on
- *                 the fly
+ *                 only (with min-max: NUFFT_ERR_UNSUPPORTED); 0: the default (a
+ *                 table for Kaiser-Bessel windows of up to 8 taps as long as it
+ *                 takes at most 256 MiB, else evaluated on the fly); the same
+ *                 weights to the bit either way
  *   fft_radix     radix schedule of the Stockham FFT passes on every axis
  *                 (Section 2.1 "Oversampled FFT"): 0: the fewest passes over
  *                 radices 2 to 6 and 8; 1: radices 4, 8, 2, 3, 5
