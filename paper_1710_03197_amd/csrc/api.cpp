@@ -397,7 +397,7 @@ int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
     // of sparse tiles along the last axis (their samples are contiguous in the
     // sorted order) share one item of at most `ichunk` samples and
     // interp_merge tiles, which stages one region for all of them.
-    const int ichunk = 256 * kInterpSamplesPerThread;
+    const int ichunk = interp_threads(d) * kInterpSamplesPerThread;
     std::vector<InterpItem> iitems;
     if (p->staged_interp) {
         const int nt_last = p->nt[d - 1];
@@ -762,7 +762,7 @@ int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s,
     a.n_items = p->n_iitems;
     a.merge = p->interp_merge;
     // (in a multi-problem launch the other problems fill the chip)
-    a.grids_per_wg = a.items && !col ? interp_grids_per_wg(a.n_items, grids) : grids;
+    a.grids_per_wg = a.items && !col ? interp_grids_per_wg(p->d, a.n_items, grids) : grids;
     for (int ax = 0; ax < p->d; ++ax) {
         a.T[ax] = p->T[ax];
         a.nt[ax] = p->nt[ax];

@@ -42,6 +42,7 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
     }
     const int P = E[DIM - 1] | 1;
     const int region = rows * P;
+    constexpr int TH = interp_threads(DIM);
     constexpr int SPT = kInterpSamplesPerThread;
     float w[SPT][DIM][J];
     int off[SPT];
@@ -50,7 +51,7 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
     int dst[SPT];  // caller's index of the sample (loaded early, used by the final store)
 #pragma unroll
     for (int k = 0; k < SPT; ++k) {
-        const int s = threadIdx.x + k * 256;
+        const int s = threadIdx.x + k * TH;
         valid[k] = s < it.count;
         off[k] = 0;
         ph[k] = make_float2(1.f, 0.f);
@@ -113,9 +114,9 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
                         (reinterpret_cast<uintptr_t>(a.G) % 16 == 0);
     // this thread's place in the row-major walk over the region's pairs: the
     // column stays fixed, the row advances by RP per round
-    const int RP = H <= 256 ? 256 / H : 1;
-    const int pr0 = H <= 256 ? int(threadIdx.x) / H : 0;
-    const int pc = H <= 256 ? int(threadIdx.x) - pr0 * H : int(threadIdx.x);
+    const int RP = H <= TH ? TH / H : 1;
+    const int pr0 = H <= TH ? int(threadIdx.x) / H : 0;
+    const int pc = H <= TH ? int(threadIdx.x) - pr0 * H : int(threadIdx.x);
     int kl = base[DIM - 1] + 2 * pc;  // grid column of the pair (< 2 K_last)
     if (kl >= KL) kl -= KL;
     const int g_lo = gg * a.grids_per_wg, g_hi = min(a.grids, g_lo + a.grids_per_wg);
@@ -123,7 +124,7 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
         const float2 *G = a.G + int64_t(g) * a.grid_elems;
         __syncthreads();
         constexpr int U = 8;  // loads in flight per thread
-        if (paired && H <= 256) {
+        if (paired && H <= TH) {
             // (2D regions are a few rows: 2 paired loads keep the registers,
             // and the occupancy, of the element path)
             constexpr int UP = DIM == 3 ? U : 2;
@@ -166,13 +167,13 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
             }
         } else {
             // element by element (odd tiles, unaligned grids, rows longer
-            // than 512 elements), U elements per thread in flight
+            // than twice the workgroup), U elements per thread in flight
             FastDiv byP(P);
-            for (int e0 = 0; e0 < region; e0 += U * 256) {
+            for (int e0 = 0; e0 < region; e0 += U * TH) {
                 float2 v[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int e = min(e0 + u * 256 + int(threadIdx.x), region - 1);
+                    const int e = min(e0 + u * TH + int(threadIdx.x), region - 1);
                     const int r = byP.div(e);
                     int k = base[DIM - 1] + byP.rem(e, r);
                     if (k >= KL) k -= KL;
@@ -180,7 +181,7 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int e = e0 + u * 256 + threadIdx.x;
+                    const int e = e0 + u * TH + threadIdx.x;
                     if (e < region) reg[e] = v[u];
                 }
             }
@@ -224,12 +225,12 @@ __device__ __forceinline__ void interp_body(const InterpArgs &a, int64_t item, i
 }
 
 template <int J, int DIM>
-__global__ __launch_bounds__(256) void k_interp(InterpArgs a) {
+__global__ __launch_bounds__(interp_threads(DIM)) void k_interp(InterpArgs a) {
     interp_body<J, DIM>(a, blockIdx.x, blockIdx.y);
 }
 
 template <int J, int DIM>
-__global__ __launch_bounds__(256) void k_interp_multi(const InterpArgs *__restrict__ jobs,
+__global__ __launch_bounds__(interp_threads(DIM)) void k_interp_multi(const InterpArgs *__restrict__ jobs,
                                                      const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     interp_body<J, DIM>(jobs[b.x], b.y, 0);
@@ -416,7 +417,7 @@ struct InterpLaunch {
         if (a.items) {
             if (a.n_items == 0) return hipSuccess;
             const unsigned gy = unsigned((a.grids + a.grids_per_wg - 1) / a.grids_per_wg);
-            launch_kernel((k_interp<J, DIM>), dim3(unsigned(a.n_items), gy), dim3(256), interp_lds(a), s, a);
+            launch_kernel((k_interp<J, DIM>), dim3(unsigned(a.n_items), gy), dim3(interp_threads(DIM)), interp_lds(a), s, a);
         } else {
             const int64_t blocks = (a.M + 255) / 256;
             launch_kernel((k_interp_direct<J, DIM>), dim3(unsigned(blocks)), dim3(256), 0, s, a);
@@ -431,7 +432,7 @@ struct InterpMultiLaunch {
                          hipStream_t s) {
         if (n == 0) return hipSuccess;
         if (staged)
-            launch_kernel((k_interp_multi<J, DIM>), dim3(unsigned(n)), dim3(256), lds, s, jobs, blocks);
+            launch_kernel((k_interp_multi<J, DIM>), dim3(unsigned(n)), dim3(interp_threads(DIM)), lds, s, jobs, blocks);
         else
             launch_kernel((k_interp_direct_multi<J, DIM>), dim3(unsigned(n)), dim3(256), 0, s, jobs, blocks);
         return hipGetLastError();

@@ -21,7 +21,13 @@ constexpr int kFftTileElems = 4096;  // complex elements of its tile (8 per thre
 constexpr int kXcds = 8;             // XCDs the hardware deals workgroups over, each with its own L2
 constexpr int kMaxLinesPerWg = 64;   // lines (contiguous-axis passes) per FFT workgroup
 constexpr int kMaxPolyDeg = 23;
-constexpr int kInterpSamplesPerThread = 2;  // gather work item = 512 samples
+constexpr int kInterpSamplesPerThread = 2;
+// Threads of a staged gather's workgroup; a work item holds at most two samples
+// per thread.  Two wavefronts in 2D: a 16 x 16 tile of the uneven spiral batch
+// holds about 125 samples, and four wavefronts left half of theirs idle (24
+// spirals x 8 coils 420 -> 342 us, 8 coils of 320 x 320 25.4 -> 22.7, one 256 x
+// 256 grid unchanged within 0.4 us).
+constexpr int interp_threads(int d) { return d == 2 ? 128 : 256; }
 constexpr int kLdsBudget = 64 * 1024;      // bytes of LDS a gather or gridding tile may use
 constexpr int kInterpLdsBudget = 64 * 1024;  // bytes of LDS a gather item covering several tiles may use
 
@@ -200,7 +206,7 @@ hipError_t launch_weight_table(const SampleGeom &g, const float *om_sorted, int6
 struct InterpItem {
     int bin;    // first tile
     int start;  // first sorted sample
-    int count;  // <= 256 * kInterpSamplesPerThread
+    int count;  // <= interp_threads(d) * kInterpSamplesPerThread
     int tiles;  // tiles along the last axis the item covers (their samples are contiguous)
 };
 struct InterpArgs {
@@ -222,13 +228,13 @@ struct InterpArgs {
 hipError_t launch_interp(const InterpArgs &a, hipStream_t s);
 // Grids (coils, batch entries) a staged gather's workgroup walks one after the
 // other, its samples' windows read or evaluated once for all of them: all,
-// unless that leaves fewer than kInterpGroups workgroups (8 per CU), since each
+// unless that leaves fewer than 2048 x 256 threads (32 wavefronts per CU), since each
 // grid is a round trip to memory between two barriers.  Measured, all -> split:
 // 24 grids of 256 x 256 with 130 items 63.8 -> 20 us; 8 grids of 640 x 640 with
 // 720 items 31.9 -> 25.4 us (4 workgroups per item).
-constexpr int64_t kInterpGroups = 2048;
-inline int interp_grids_per_wg(int64_t items, int grids) {
-    return int(std::max<int64_t>(1, std::min<int64_t>(grids, items * grids / kInterpGroups)));
+inline int interp_grids_per_wg(int d, int64_t items, int grids) {
+    const int64_t groups = 2048 * 256 / interp_threads(d);
+    return int(std::max<int64_t>(1, std::min<int64_t>(grids, items * grids / groups)));
 }
 // Elements of a gather item's LDS region: the tiles (merge of them along the
 // last axis) plus the J - 1 halo, the last axis made odd.
