@@ -874,7 +874,7 @@ constexpr int kMultiCache = 4;  // pointer sets kept per direction
 struct MultiLaunch {
     int kind = 0;
     int threads = 0;
-    bool inverse = false, split = false, staged = false, coils = false;
+    bool inverse = false, split = false, wide = false, staged = false, coils = false;
     GridArgs proto{};  // gridding: the kernel instance
     int J = 0, d = 0;
     size_t lds = 0;
@@ -1005,15 +1005,15 @@ void stage_blocks(const Emitted &em, int job, int threads, std::vector<int4> &ou
 
 // Key of the kernel instance a recorded launch uses (launches with equal keys
 // in one slot share a multi-problem launch).  FFT passes share one
-// workgroup size per slot (the largest any problem needs), so only the
-// strided pass's direction and split-tile form and
-// the last pass's coils separate them.
+// workgroup size per slot (the largest any problem needs), so only the coils
+// of the first and last pass and the strided pass's direction, split-tile form
+// and offset width separate them.
 int64_t stage_key(const Emitted &em) {
     switch (em.kind) {
         case kStFirst: return em.first.coils ? 1 : 0;
         case kStStrided: {
             const bool split = em.strided.inverse && em.strided.split_of_tile != nullptr;
-            return (em.strided.inverse ? 2 : 0) + (split ? 1 : 0);
+            return (strided_wide(em.strided) ? 4 : 0) + (em.strided.inverse ? 2 : 0) + (split ? 1 : 0);
         }
         case kStLast: return (last_pass_coils(em.last) ? 1 : 0);
         case kStInterp: return em.interp.items ? 1 : 0;
@@ -1121,6 +1121,7 @@ int build_call(nufft_multi_s *m, bool forward, const void *const *in, void *cons
                         L.lds = std::max(L.lds, fl.lds);
                         L.inverse = em->strided.inverse;
                         L.split = em->strided.inverse && em->strided.split_of_tile != nullptr;
+                        L.wide = strided_wide(em->strided);
                     }
                     e = upload_jobs(jobs, &L.jobs);
                     break;
@@ -1188,7 +1189,7 @@ hipError_t issue(const MultiLaunch &L, hipStream_t s) {
                                            L.coils, L.lds, s);
         case kStStrided:
             return launch_strided_pass_multi(static_cast<const StridedJob *>(L.jobs), L.blocks, L.nblocks, L.threads,
-                                             L.inverse, L.split, L.lds, s);
+                                             L.inverse, L.split, L.wide, L.lds, s);
         case kStLast:
             return launch_last_pass_multi(static_cast<const LastJob *>(L.jobs), L.blocks, L.nblocks, L.threads,
                                           L.coils, L.lds, s);

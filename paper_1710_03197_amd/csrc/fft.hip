@@ -242,12 +242,14 @@ struct TwiddleStage {
     }
 };
 
-// p[off] for a uniform p and a lane's offset of less than 2^32 bytes: a scalar
-// base and one 32-bit register per address.
-__device__ __forceinline__ float2 load_at(const float2 *p, unsigned off_bytes) {
+// p[off] for a uniform p and a lane's byte offset: with a 32-bit offset a scalar
+// base and one register per address.
+template <class Off>
+__device__ __forceinline__ float2 load_at(const float2 *p, Off off_bytes) {
     return *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(p) + off_bytes);
 }
-__device__ __forceinline__ void store_at(float2 *p, unsigned off_bytes, float2 v) {
+template <class Off>
+__device__ __forceinline__ void store_at(float2 *p, Off off_bytes, float2 v) {
     *reinterpret_cast<float2 *>(reinterpret_cast<char *>(p) + off_bytes) = v;
 }
 
@@ -524,13 +526,15 @@ struct TileMap {
 // keep their register budget: the first inverse pass of an adjoint whose split
 // gridding tiles are still partial tiles, and the first inverse pass after a
 // Toeplitz product.  A tile's lanes address one slab of K rows by inner columns
-// from scalar row bases; (K / R) rows of it hold less than 2^32 bytes for
-// radices of at least 4, which the first and last radix are wherever a slab
-// reaches 4 GiB (launch_strided_pass checks).
+// from scalar row bases, K / R rows apart (R the first radix on the way in, the
+// last on the way out).  WIDE: those rows hold more than 4 GiB and the lanes'
+// offsets are 64 bits wide (strided_wide); everywhere else they are 32 bits, one
+// register per address instead of two.
 enum { kPlain, kSplitTiles, kProduct };
-template <bool INV, int FORM>
+template <bool INV, int FORM, bool WIDE>
 __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int W, int64_t ntc, int64_t bid) {
     extern __shared__ float2 lds[];
+    using Off = std::conditional_t<WIDE, uint64_t, unsigned>;
     const int K = a.K;
     float2 *tw = lds;
     float2 *s = lds + K;
@@ -549,7 +553,7 @@ __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int 
     // centring shift when Lin == K); inverse: the input is the grid
     auto load = [&](int w, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
         constexpr int R = decltype(RC)::value;
-        const unsigned off = (unsigned(j) * unsigned(a.inner) + unsigned(w)) * unsigned(sizeof(float2));
+        const Off off = (Off(j) * unsigned(a.inner) + unsigned(w)) * unsigned(sizeof(float2));
         if constexpr (FORM == kSplitTiles) {
             // First inverse pass of the adjoint: a cell of a split gridding tile
             // is the sum of its partial tiles in chunk order (the order, hence
@@ -642,7 +646,7 @@ __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int 
     with_radix(a.rp.r[a.rp.n - 1], [&](auto RL) NUFFT_INLINE {
         last_radix<RL, true>(s, wv, 1, wv, a.rp, tw, [&](int w, int j, int nbl, auto RC, float2 *v) NUFFT_INLINE {
             constexpr int R = decltype(RC)::value;
-            const unsigned off = (unsigned(j) * unsigned(a.inner) + unsigned(w)) * unsigned(sizeof(float2));
+            const Off off = (Off(j) * unsigned(a.inner) + unsigned(w)) * unsigned(sizeof(float2));
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const int q0 = u * nbl;
@@ -659,17 +663,17 @@ __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int 
     });
 }
 
-template <bool INV, int FORM>
+template <bool INV, int FORM, bool WIDE = false>
 __global__ __launch_bounds__(kFftThreads) void k_strided_pass(StridedPassArgs a, int W, int64_t ntc) {
-    strided_pass_body<INV, FORM>(a, W, ntc, xcd_block(blockIdx.x, gridDim.x));
+    strided_pass_body<INV, FORM, WIDE>(a, W, ntc, xcd_block(blockIdx.x, gridDim.x));
 }
 
-template <bool INV, int FORM>
+template <bool INV, int FORM, bool WIDE = false>
 __global__ __launch_bounds__(kFftThreads) void k_strided_pass_multi(const StridedJob *__restrict__ jobs,
                                                                const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const StridedJob &j = jobs[b.x];
-    strided_pass_body<INV, FORM>(j.a, j.W, j.ntc, b.y);
+    strided_pass_body<INV, FORM, WIDE>(j.a, j.W, j.ntc, b.y);
 }
 
 template <bool COILS>
@@ -866,25 +870,30 @@ FftLaunch strided_pass_launch(const StridedPassArgs &a, int threads) {
     return L;
 }
 
-// A lane's byte offsets within its slab fit 32 bits in the first and last pass.
-bool strided_offsets_fit(const StridedPassArgs &a) {
-    const double slab = double(a.inner) * sizeof(float2);
-    return slab * a.rp.nbl[0] < 4294967296.0 && slab * a.rp.nbl[a.rp.n - 1] < 4294967296.0;
-}
-
 hipError_t launch_strided_pass(const StridedPassArgs &a, hipStream_t s) {
     const FftLaunch L = strided_pass_launch(a);
     if (L.blocks == 0) return hipSuccess;
-    if (!strided_offsets_fit(a)) return hipErrorInvalidValue;
+    const bool wide = strided_wide(a);
     const dim3 grid{unsigned(L.blocks)}, block{unsigned(L.threads)};
-    if (!a.inverse)
-        launch_kernel((k_strided_pass<false, kPlain>), grid, block, L.lds, s, a, L.p0, L.p1);
-    else if (a.split_of_tile)
-        launch_kernel((k_strided_pass<true, kSplitTiles>), grid, block, L.lds, s, a, L.p0, L.p1);
-    else if (a.mult)
+    if (!a.inverse) {
+        if (wide)
+            launch_kernel((k_strided_pass<false, kPlain, true>), grid, block, L.lds, s, a, L.p0, L.p1);
+        else
+            launch_kernel((k_strided_pass<false, kPlain>), grid, block, L.lds, s, a, L.p0, L.p1);
+    } else if (a.split_of_tile) {
+        if (wide)
+            launch_kernel((k_strided_pass<true, kSplitTiles, true>), grid, block, L.lds, s, a, L.p0, L.p1);
+        else
+            launch_kernel((k_strided_pass<true, kSplitTiles>), grid, block, L.lds, s, a, L.p0, L.p1);
+    } else if (a.mult) {
+        // (a Toeplitz grid's lengths are multiples of 4: its first radix is 4 or more, never wide)
+        if (wide) return hipErrorInvalidValue;
         launch_kernel((k_strided_pass<true, kProduct>), grid, block, L.lds, s, a, L.p0, L.p1);
-    else
+    } else if (wide) {
+        launch_kernel((k_strided_pass<true, kPlain, true>), grid, block, L.lds, s, a, L.p0, L.p1);
+    } else {
         launch_kernel((k_strided_pass<true, kPlain>), grid, block, L.lds, s, a, L.p0, L.p1);
+    }
     return hipGetLastError();
 }
 
@@ -939,13 +948,19 @@ hipError_t launch_first_pass_multi(const FirstJob *jobs, const int4 *blocks, int
 }
 
 hipError_t launch_strided_pass_multi(const StridedJob *jobs, const int4 *blocks, int64_t nblocks, int threads,
-                                     bool inverse, bool split, size_t lds, hipStream_t s) {
+                                     bool inverse, bool split, bool wide, size_t lds, hipStream_t s) {
     if (nblocks == 0) return hipSuccess;
     const dim3 grid{unsigned(nblocks)}, block{unsigned(threads)};
-    if (!inverse)
+    if (!inverse && wide)
+        launch_kernel((k_strided_pass_multi<false, kPlain, true>), grid, block, lds, s, jobs, blocks);
+    else if (!inverse)
         launch_kernel((k_strided_pass_multi<false, kPlain>), grid, block, lds, s, jobs, blocks);
+    else if (split && wide)
+        launch_kernel((k_strided_pass_multi<true, kSplitTiles, true>), grid, block, lds, s, jobs, blocks);
     else if (split)
         launch_kernel((k_strided_pass_multi<true, kSplitTiles>), grid, block, lds, s, jobs, blocks);
+    else if (wide)
+        launch_kernel((k_strided_pass_multi<true, kPlain, true>), grid, block, lds, s, jobs, blocks);
     else
         launch_kernel((k_strided_pass_multi<true, kPlain>), grid, block, lds, s, jobs, blocks);
     return hipGetLastError();

@@ -343,8 +343,9 @@ bool radix_plan(int K, RadixPlan *rp, int schedule) {
     }
     if (r.size() == 1) r.push_back(1);
     if (int(r.size()) > kMaxPasses) return false;
-    // long lines start and end with a radix of at least 4: the strided passes
-    // address K / r rows by 32-bit offsets, which then reach any grid
+    // long lines start and end with a radix of at least 4 where they have one:
+    // the strided passes address K / r rows at a time, by 32-bit offsets as long
+    // as those rows hold at most 4 GiB (strided_wide)
     if (K > 64) {
         auto wide = [&](int q) { return q >= 4; };
         if (!wide(r.front()))

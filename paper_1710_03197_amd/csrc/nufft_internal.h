@@ -153,6 +153,16 @@ struct StridedPassArgs {
     const float2 *phase;  // min-max grid phase e^{-i pi k / K} of this pass's axis (nullptr: none)
 };
 hipError_t launch_strided_pass(const StridedPassArgs &a, hipStream_t s);
+// Whether a lane's byte offsets of a strided pass need more than 32 bits: it
+// addresses K / R rows of inner cells from each row base, R the first radix of
+// an inverse pass (its loads) or the last radix of a forward one (its stores).
+// With R of 4 or more they never do (a grid holds less than 2^31 cells), but
+// lengths such as 162, 486 and 1458 end in 3, and other schedules start or end
+// in 2 and 3 more often.
+inline bool strided_wide(const StridedPassArgs &a) {
+    const uint64_t rows = uint64_t(a.rp.nbl[a.inverse ? 0 : a.rp.n - 1]);
+    return rows * uint64_t(a.inner) * sizeof(float2) > (uint64_t(1) << 32);
+}
 
 // Inverse pass along the contiguous last axis with crop K -> N, scaling and
 // coil combination: in [B*C][rows][K] -> x [B][rows][N].
@@ -502,7 +512,7 @@ struct PermuteJob {
 hipError_t launch_first_pass_multi(const FirstJob *jobs, const int4 *blocks, int64_t nblocks, int threads, bool coils,
                                    size_t lds, hipStream_t s);
 hipError_t launch_strided_pass_multi(const StridedJob *jobs, const int4 *blocks, int64_t nblocks, int threads,
-                                     bool inverse, bool split, size_t lds, hipStream_t s);
+                                     bool inverse, bool split, bool wide, size_t lds, hipStream_t s);
 hipError_t launch_last_pass_multi(const LastJob *jobs, const int4 *blocks, int64_t nblocks, int threads, bool coils,
                                   size_t lds, hipStream_t s);
 // LDS of a staged gather launch (0 for the direct form).

@@ -1,0 +1,154 @@
+"""The runtime's host code on the CPU: api.cpp and kb_host.cpp linked against
+stand-ins for the HIP runtime and the kernel launchers (host_stub.cpp), which
+log streams, allocations and launches."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1710_03197_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1710_03197_amd", "csrc")
+HERE = os.path.dirname(os.path.abspath(__file__))
+CXX = ["g++", "-O1", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", f"-I{ROOT}/include",
+       f"-I{CSRC}"]
+
+if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+    pytest.skip("needs g++ and the HIP headers", allow_module_level=True)
+
+
+@pytest.fixture(scope="module")
+def objects(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host")
+    procs = []
+    for src in (os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "kb_host.cpp"), os.path.join(HERE, "host_stub.cpp")):
+        obj = str(d / (os.path.basename(src) + ".o"))
+        procs.append((obj, subprocess.Popen([*CXX, "-c", src, "-o", obj])))
+    assert all(p.wait() == 0 for _, p in procs)
+    return d, [obj for obj, _ in procs]
+
+
+class Host:
+    """The library's entry points over the stand-ins."""
+
+    def __init__(self, path):
+        self.lib = ctypes.CDLL(path)
+        for name, args in _lib._SIGS.items():
+            getattr(self.lib, name).argtypes = args
+        self.lib.nufft_last_error.restype = self.lib.stub_log.restype = ctypes.c_char_p
+        self.lib.stub_fail_allocations.argtypes = [ctypes.c_size_t, ctypes.c_int]
+        self.lib.stub_live_bytes.restype = ctypes.c_size_t
+        self.keep = []
+
+    def call(self, name, *args, status=0):
+        self.lib.stub_clear()
+        st = getattr(self.lib, name)(*args)
+        assert st == status, (name, st, self.lib.nufft_last_error())
+        return [dict([("what", line.split()[0])] + [kv.split("=") for kv in line.split()[1:]])
+                for line in self.lib.stub_log().decode().splitlines()]
+
+    def points(self, om):
+        om = np.ascontiguousarray(om, dtype=np.float32)
+        self.keep.append(om)
+        return om.ctypes.data
+
+    def plan(self, N, K, J, om, stream=None, **options):
+        from paper_1710_03197_amd.plan import options_struct
+        opt = options_struct(options)
+        h = ctypes.c_void_p()
+        i64 = ctypes.c_int64 * len(N)
+        log = self.call("nufft_plan_ex", len(N), i64(*N), i64(*K), J, len(om), self.points(om), ctypes.byref(opt),
+                        stream, ctypes.byref(h))
+        return h, log
+
+    def multi(self, problems):
+        """problems: (N, K, J, om, coils, options)."""
+        from paper_1710_03197_amd.plan import options_struct
+        descs = (_lib.ProblemDesc * len(problems))()
+        for de, (N, K, J, om, C, options) in zip(descs, problems):
+            de.d, de.J, de.M, de.om = len(N), J, len(om), self.points(om)
+            de.N[:len(N)], de.K[:len(K)] = N, K
+            if C:
+                maps = np.ones((C,) + tuple(N), np.complex64)
+                self.keep.append(maps)
+                de.C, de.coils = C, maps.ctypes.data
+            opt = options_struct(options)
+            self.keep.append(opt)
+            de.opt = ctypes.addressof(opt)
+        h = ctypes.c_void_p()
+        self.call("nufft_multi_plan", len(problems), descs, None, ctypes.byref(h))
+        return h
+
+
+@pytest.fixture(scope="module")
+def host(objects):
+    d, objs = objects
+    so = str(d / "libhost.so")
+    subprocess.run(["g++", "-shared", *objs, "-o", so], check=True)
+    return Host(so)
+
+
+def _buf(n=1):
+    return ctypes.c_void_p(0x1000 + n)  # never dereferenced: nothing runs
+
+
+# ---- 32-bit offsets of the strided FFT passes
+OFFSETS = r"""
+#include <cstdio>
+#include "nufft_internal.h"
+using namespace nufft;
+int main() {
+    long wide_n = 0;
+    for (int K = 2; K <= 4096; K += 2)
+        for (int sched = 0; sched < 4; ++sched) {
+            StridedPassArgs a{};
+            if (!radix_plan(K, &a.rp, sched)) continue;
+            a.K = K;
+            // the largest array of the axis: below 2^31 cells, two axes of at most 4096 after it
+            for (int64_t inner : {std::min<int64_t>(4096 * 4096, ((int64_t(1) << 31) - 1) / K), int64_t(4096)}) {
+                a.inner = inner;
+                for (bool inverse : {false, true}) {
+                    a.inverse = inverse;
+                    const int p = inverse ? 0 : a.rp.n - 1;
+                    const int64_t last = (int64_t(a.rp.nbl[p] - 1) * inner + inner - 1) * 8;
+                    if (strided_wide(a) != (last >= int64_t(1) << 32)) {
+                        printf("K=%d schedule %d inner %lld\n", K, sched, (long long)inner);
+                        return 1;
+                    }
+                    wide_n += strided_wide(a);
+                    // Toeplitz grids (2N, N even, the default schedule) take no wide pass
+                    if (K % 4 == 0 && sched == 0 && strided_wide(a)) return 2;
+                }
+            }
+        }
+    printf("%ld\n", wide_n);
+    return wide_n > 0 ? 0 : 3;
+}
+"""
+
+
+def test_strided_offset_width_covers_every_length(objects):
+    """Over every grid length and radix schedule at the largest array: offsets
+    are 64 bits wide exactly where 32 do not reach."""
+    d, objs = objects
+    src, exe = d / "offsets.cpp", d / "offsets"
+    src.write_text(OFFSETS)
+    kb = [o for o in objs if "kb_host" in o]
+    subprocess.run([*CXX, str(src), *kb, "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, (out.returncode, out.stdout)
+
+
+def test_multi_problem_passes_take_the_offset_width_of_each_problem(host):
+    """A grid whose forward pass along axis 0 ends in radix 3 over 4 GiB of rows,
+    beside a small one: two launches, the large one wide."""
+    om = np.full((4, 3), 0.5, np.float32)
+    m = host.multi([((2, 2, 2), (162, 4096, 3200), 6, om, 0, {}), ((8, 8, 8), (16, 16, 16), 6, om, 0, {})])
+    ptrs = (ctypes.c_void_p * 2)(_buf(1), _buf(2))
+    log = [e for e in host.call("nufft_multi_forward", m, ptrs, ptrs, None) if e["what"] == "strided_multi"]
+    assert [(e["K"], e["wide"]) for e in log] == [("4096", "0"), ("162", "1"), ("16", "0")]
+    host.call("nufft_multi_destroy", m)
