@@ -164,6 +164,7 @@ struct nufft_plan_s {
     float2 *ysorted = nullptr;  // [cap_grids][M] samples in sorted order for the gridding
     float2 *dc = nullptr;       // [2][M] sample buffers of the density compensation, from its first call on
     hipStream_t last_stream = nullptr;
+    bool called = false;  // last_stream is a call's (it may be the default stream, NULL)
     // optional per-kernel event timing
     bool timing = false;
     struct TimingRec {
@@ -860,6 +861,7 @@ int begin_call(nufft_plan_t plan, void *stream) {
     if (st) return st;
     HIP_TRY(hipSetDevice(plan->device), "select device");
     plan->last_stream = static_cast<hipStream_t>(stream);
+    plan->called = true;
     return NUFFT_OK;
 }
 
@@ -1725,14 +1727,15 @@ int nufft_set_points(nufft_plan_t plan, const float *om_dev, void *stream) {
     int st = check_plan(plan);
     if (st) return st;
     const hipStream_t prev_stream = plan->last_stream;
+    const bool called = plan->called;
     st = begin_call(plan, stream);
     if (st) return st;
     if (plan->M > 0 && !om_dev) return fail(NUFFT_ERR_INVALID_ARG, "om is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
     // The tables below are rewritten in place: wait for the plan's previous
-    // call (possibly on another stream) first.  Keep the previous trajectory
-    // if the new one is rejected.
-    if (prev_stream && prev_stream != s) HIP_TRY(hipStreamSynchronize(prev_stream), "wait for the previous call");
+    // call (possibly on another stream, the default stream among them) first.
+    // Keep the previous trajectory if the new one is rejected.
+    if (called && prev_stream != s) HIP_TRY(hipStreamSynchronize(prev_stream), "wait for the previous call");
     const size_t bytes = size_t(plan->M) * plan->d * sizeof(float);
     if (plan->M > 0) HIP_TRY(hipMemcpyAsync(plan->om_prev, plan->om, bytes, hipMemcpyDeviceToDevice, s),
                              "backup trajectory");

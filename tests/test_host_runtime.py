@@ -152,3 +152,28 @@ def test_multi_problem_passes_take_the_offset_width_of_each_problem(host):
     log = [e for e in host.call("nufft_multi_forward", m, ptrs, ptrs, None) if e["what"] == "strided_multi"]
     assert [(e["K"], e["wide"]) for e in log] == [("4096", "0"), ("162", "1"), ("16", "0")]
     host.call("nufft_multi_destroy", m)
+
+
+# ---- re-binning a plan in use
+@pytest.mark.parametrize("before,now,waits", [(None, 16, True), (32, 16, True), (16, None, True), (16, 16, False),
+                                              (None, None, False)])
+def test_set_points_waits_for_the_previous_calls_stream(host, before, now, waits):
+    """Re-binning on another stream than the previous call's, the default stream
+    (NULL) among them, waits for that stream before it writes anything."""
+    om = np.full((50, 2), 0.5, np.float32)
+    p, _ = host.plan((16, 16), (32, 32), 6, om)
+    host.call("nufft_forward", p, _buf(1), _buf(2), before)
+    log = host.call("nufft_set_points", p, host.points(om), now)
+    name = {None: "(nil)"}.get(before, f"{before or 0:#x}")
+    first_write = next(i for i, e in enumerate(log) if e["what"] == "write")
+    waited = [e["stream"] for e in log[:first_write] if e["what"] == "sync"]
+    assert waited == ([name] if waits else [])
+    host.call("nufft_destroy", p)
+
+
+def test_set_points_of_an_uncalled_plan_waits_for_no_stream(host):
+    om = np.full((50, 2), 0.5, np.float32)
+    p, _ = host.plan((16, 16), (32, 32), 6, om)
+    log = host.call("nufft_set_points", p, host.points(om), 16)
+    assert log[0]["what"] == "write"
+    host.call("nufft_destroy", p)
