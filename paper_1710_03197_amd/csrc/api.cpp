@@ -116,7 +116,8 @@ struct nufft_plan_s {
     float *om = nullptr;
     float *om_sorted = nullptr;
     int *perm = nullptr;
-    // work lists, all inside `tables` (grown, never shrunk)
+    // work lists, all inside `tables` (grown, never shrunk); without them
+    // (a re-bin that found no memory) transforms are refused
     char *tables = nullptr;
     size_t cap_tables = 0;
     GridItem *items = nullptr;
@@ -493,10 +494,20 @@ int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
     }
     if (total > p->cap_tables) {
         HIP_TRY(hipStreamSynchronize(s), "binning the trajectory");
+        // The old lists stay until there is room for the new ones, so a re-bin
+        // that fails leaves a plan whose lists are whole.
+        size_t cap = total + total / 4;  // room for the next trajectory's lists
+        char *fresh = nullptr;
+        if (dmalloc(&fresh, cap) != hipSuccess) {
+            (void)hipGetLastError();
+            // only without the old ones: the caller bins the old trajectory again if not even then
+            dfree(p->tables);
+            p->cap_tables = 0;
+            cap = total;
+            HIP_TRY(dmalloc(&fresh, cap), "allocate work lists");
+        }
         dfree(p->tables);
-        p->cap_tables = 0;
-        const size_t cap = total + total / 4;  // room for the next trajectory's lists
-        HIP_TRY(dmalloc(&p->tables, cap), "allocate work lists");
+        p->tables = fresh;
         p->cap_tables = cap;
     }
     p->split_of_tile = reinterpret_cast<int2 *>(p->tables + at_split);
@@ -750,6 +761,7 @@ int run_shfh(nufft_plan_s *p, const FftGeom &f, const float2 *h, int B, float2 *
 // sorted: the samples are left in the plan's sorted order.
 int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s, Collector *col = nullptr,
           bool sorted = false) {
+    if (!p->tables) return fail(NUFFT_ERR_OOM, "the plan lost its work lists in a re-bin without memory");
     InterpArgs a{};
     a.geo = p->geom();
     a.om_sorted = p->om_sorted;
@@ -781,6 +793,7 @@ int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s,
 // the plan's sorted order already.
 int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s, bool reduce = true,
            Collector *col = nullptr, bool sorted = false) {
+    if (!p->tables) return fail(NUFFT_ERR_OOM, "the plan lost its work lists in a re-bin without memory");
     const bool permute = p->presort && !sorted;
     if (permute) {
         if (col)

@@ -177,3 +177,31 @@ def test_set_points_of_an_uncalled_plan_waits_for_no_stream(host):
     log = host.call("nufft_set_points", p, host.points(om), 16)
     assert log[0]["what"] == "write"
     host.call("nufft_destroy", p)
+
+
+def _trajectories(M=200000):
+    """One whose samples share a tile (few work items) and one dealt over all tiles (many)."""
+    return np.full((M, 2), -0.5, np.float32), np.full((M, 2), 0.5, np.float32)
+
+
+@pytest.mark.parametrize("failures", [0, 1, 2, 3, 4])
+def test_rebin_without_memory_leaves_no_dangling_lists(host, failures):
+    """Larger work lists whose allocation fails: once, the old ones make room;
+    two or three times, the re-bin reports it and the plan keeps its previous
+    trajectory; four times, not even that one's lists fit again and transforms are
+    refused.  No launch reads freed lists in any case."""
+    few, many = _trajectories()
+    p, _ = host.plan((64, 64), (128, 128), 6, few)
+    host.lib.stub_fail_allocations(4096, failures)
+    host.call("nufft_set_points", p, host.points(many), None, status=-3 if failures > 1 else 0)
+    for name in ("nufft_forward", "nufft_adjoint"):
+        log = host.call(name, p, _buf(1), _buf(2), None, status=-3 if failures > 3 else 0)
+        launches = [e for e in log if e["what"] in ("grid", "interp", "reduce")]
+        assert bool(launches) == (failures < 4)
+        assert all(e["live"] == "1" for e in launches)
+    host.lib.stub_fail_allocations(0, 0)
+    # with memory again, a re-bin makes the plan whole
+    host.call("nufft_set_points", p, host.points(many), None)
+    log = host.call("nufft_adjoint", p, _buf(1), _buf(2), None)
+    assert [e["live"] for e in log if e["what"] in ("grid", "reduce")][0] == "1"
+    host.call("nufft_destroy", p)
