@@ -120,10 +120,11 @@ int nufft_plan(int d, const int64_t *N, const int64_t *K, int J, int64_t M,
  *                 gridding and the staged interpolation read it instead of
  *                 evaluating the kernel per sample (the paper's precomputed
  *                 interpolator, Section 2.1 "Interpolation"); Kaiser-Bessel
- *                 only (with min-max: NUFFT_ERR_UNSUPPORTED); 0: the default (a
- *                 table for Kaiser-Bessel windows of up to 8 taps as long as it
- *                 takes at most 256 MiB, else evaluated on the fly); the same
- *                 weights to the bit either way
+ *                 only (with min-max: NUFFT_ERR_UNSUPPORTED); -1: never a
+ *                 table, evaluated on the fly; 0: the default (a table for
+ *                 Kaiser-Bessel windows of up to 8 taps as long as it takes
+ *                 at most 256 MiB, else on the fly); the same weights to the
+ *                 bit in every case
  *   fft_radix     radix schedule of the Stockham FFT passes on every axis
  *                 (Section 2.1 "Oversampled FFT"): 0: the fewest passes over
  *                 radices 2 to 6 and 8; 1: radices 4, 8, 2, 3, 5

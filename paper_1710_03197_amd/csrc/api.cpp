@@ -1555,17 +1555,21 @@ int nufft_plan_ex(int d, const int64_t *N, const int64_t *K, int J, int64_t M, c
     if (opt && opt->grid_waves != 0 && opt->grid_waves != 1 && opt->grid_waves != 4)
         return bail(fail(NUFFT_ERR_INVALID_ARG, "grid_waves takes 0, 1 or 4"));
     p->grid_waves = (opt && opt->grid_waves == 1) ? 1 : 4;
-    if (opt && (opt->weight_table < 0 || opt->weight_table > 1))
-        return bail(fail(NUFFT_ERR_INVALID_ARG, "weight_table takes 0 or 1"));
+    if (opt && (opt->weight_table < -1 || opt->weight_table > 1))
+        return bail(fail(NUFFT_ERR_INVALID_ARG, "weight_table takes -1, 0 or 1"));
     // The window table by default: the sample kernels read a record instead of
     // evaluating d J polynomials per visit.  Measured, on the fly -> table, a
     // pass: 64 x 64 pair 45.4 -> 39.7 us, 8 coils of 320 x 320 139 -> 131, 3D
     // 96 x 72 x 60 136 -> 120, 3D density compensation 634 -> 554.  Windows wider
-    // than 8 taps gain nothing (their gridding evaluates anyway), and a table
-    // above kDefaultTableBytes is left to who asks for it.
+    // than 8 taps gain nothing (their gridding evaluates anyway).  The limit is
+    // where it stops paying in 2D, at the size of the last-level cache: radial
+    // pairs on a 1024 x 1024 grid, 3.1 M samples (192 MiB) 251 -> 232 us, 4.2 M (256
+    // MiB) 311 -> 309, 8.4 M (512 MiB) 549 -> 578.  In 3D (256^3 grid) it goes on
+    // paying, 4.2 M samples (320 MiB) 1341 -> 1202 us, 16.8 M (1.25 GiB) 4226 -> 3813;
+    // memory of that order is left to who asks for it.
     constexpr int64_t kDefaultTableBytes = int64_t(256) << 20;
     p->use_wtab = p->wtab_asked = opt && opt->weight_table == 1;
-    if (!p->use_wtab && !p->minmax && J <= 8)
+    if (!p->use_wtab && !p->minmax && J <= 8 && !(opt && opt->weight_table == -1))
         p->use_wtab = M * table_stride(d, J) * int64_t(sizeof(float)) <= kDefaultTableBytes;
     if (p->use_wtab && p->minmax)
         return bail(fail(NUFFT_ERR_UNSUPPORTED, "the window table holds Kaiser-Bessel weights only"));
@@ -2025,8 +2029,11 @@ int nufft_toeplitz_plan(nufft_plan_t plan, const float *w_dev, void *stream, nuf
         destroy_toeplitz(t.get());
         return hip_fail(e, "allocate Toeplitz buffers");
     }
-    // p = adjoint NUFFT of the weights with image 2N on grid 2K (same J)
-    st = nufft_plan_ex(d, N2, K2, plan->J, M, plan->om, nullptr, stream, &pp);
+    // p = adjoint NUFFT of the weights with image 2N on grid 2K (same J); one
+    // transform, so windows are not worth a table
+    nufft_options_t popt{};
+    popt.weight_table = -1;
+    st = nufft_plan_ex(d, N2, K2, plan->J, M, plan->om, &popt, stream, &pp);
     if (!st) st = nufft_adjoint(pp, wdev, psf, stream);
     if (!st) st = ensure_toeplitz_workspace(t.get(), 1);
     if (!st) {

@@ -205,3 +205,39 @@ def test_rebin_without_memory_leaves_no_dangling_lists(host, failures):
     log = host.call("nufft_adjoint", p, _buf(1), _buf(2), None)
     assert [e["live"] for e in log if e["what"] in ("grid", "reduce")][0] == "1"
     host.call("nufft_destroy", p)
+
+
+# ---- the window table
+@pytest.mark.parametrize("option,d,M,table", [
+    (0, 2, 1000, True), (1, 2, 1000, True), (-1, 2, 1000, False),
+    (0, 3, 3355443, True), (0, 3, 3355444, False),  # 80 bytes a sample, 256 MiB
+    (1, 3, 3355444, True),
+])
+def test_window_table_option(host, option, d, M, table):
+    """0 takes a table within its limit, 1 always, -1 never."""
+    p, log = host.plan((16,) * d, (32,) * d, 6, np.full((M, d), 0.5, np.float32), weight_table=option)
+    assert [e for e in log if e["what"] == "table"] == ([dict(what="table")] if table else [])
+    for name, what in (("nufft_forward", "interp"), ("nufft_adjoint", "grid")):
+        log = host.call(name, p, _buf(1), _buf(2), None)
+        assert [e["table"] for e in log if e["what"] == what] == [str(int(table))]
+    host.call("nufft_destroy", p)
+
+
+def test_window_table_option_range(host):
+    from paper_1710_03197_amd.plan import options_struct
+    om = np.full((10, 2), 0.5, np.float32)
+    i64 = ctypes.c_int64 * 2
+    for bad in (-2, 2):
+        h = ctypes.c_void_p()
+        host.call("nufft_plan_ex", 2, i64(16, 16), i64(32, 32), 6, 10, host.points(om),
+                  ctypes.byref(options_struct(dict(weight_table=bad))), None, ctypes.byref(h), status=-1)
+
+
+def test_toeplitz_spectrum_is_made_without_a_table(host):
+    """Its point-spread function is one transform of a plan that then goes."""
+    p, _ = host.plan((16, 16), (32, 32), 6, np.full((1000, 2), 0.5, np.float32))
+    t = ctypes.c_void_p()
+    log = host.call("nufft_toeplitz_plan", p, None, None, ctypes.byref(t))
+    assert [e for e in log if e["what"] == "table"] == []
+    host.call("nufft_toeplitz_destroy", t)
+    host.call("nufft_destroy", p)
