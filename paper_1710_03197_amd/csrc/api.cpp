@@ -525,8 +525,7 @@ int bin_points(nufft_plan_s *p, const float *om_dev, hipStream_t s) {
 }
 
 // Workspace for `grids` simultaneous K^d grids.
-int ensure_workspace(nufft_plan_s *p, int grids) {
-    if (grids <= p->cap_grids && p->n_slots <= p->cap_slots) return NUFFT_OK;
+int grow_workspace(nufft_plan_s *p, int grids) {
     const int g = std::max(grids, p->cap_grids);
     if (g > p->cap_grids) {
         dfree(p->grid);
@@ -545,6 +544,20 @@ int ensure_workspace(nufft_plan_s *p, int grids) {
     p->cap_grids = g;
     p->cap_slots = p->n_slots;
     return NUFFT_OK;
+}
+
+int ensure_workspace(nufft_plan_s *p, int grids) {
+    if (grids <= p->cap_grids && p->n_slots <= p->cap_slots) return NUFFT_OK;
+    int st = grow_workspace(p, grids);
+    if (st == NUFFT_ERR_OOM && p->wtab && !p->wtab_asked) {
+        // a table nobody asked for gives way to the transforms' own memory
+        (void)hipGetLastError();
+        dfree(p->wtab);
+        p->cap_wtab = 0;
+        p->use_wtab = false;
+        st = grow_workspace(p, grids);
+    }
+    return st;
 }
 
 // ---- stage sequences

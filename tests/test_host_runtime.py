@@ -241,3 +241,17 @@ def test_toeplitz_spectrum_is_made_without_a_table(host):
     assert [e for e in log if e["what"] == "table"] == []
     host.call("nufft_toeplitz_destroy", t)
     host.call("nufft_destroy", p)
+
+
+@pytest.mark.parametrize("option,status", [(0, 0), (1, -3)])
+def test_default_table_gives_way_to_the_workspace(host, option, status):
+    """A workspace that does not fit beside a table taken by default fits without
+    it; a table that was asked for stays."""
+    p, _ = host.plan((16, 16), (32, 32), 6, np.full((1000, 2), 0.5, np.float32), weight_table=option)
+    host.lib.stub_fail_allocations(4096, 1)
+    log = host.call("nufft_forward_batched", p, 8, _buf(1), _buf(2), None, status=status)
+    assert [(e["table"], e["live"]) for e in log if e["what"] == "interp"] == ([("0", "1")] if status == 0 else [])
+    host.lib.stub_fail_allocations(0, 0)
+    log = host.call("nufft_adjoint_batched", p, 8, _buf(1), _buf(2), None)
+    assert [(e["table"], e["live"]) for e in log if e["what"] == "grid"] == [("01"[option], "1")]
+    host.call("nufft_destroy", p)
