@@ -84,74 +84,27 @@ __device__ __forceinline__ void dft<8>(float2 *v) {
     v[7] = make_float2(fmaf(-t3.x, r2, e[3].x), fmaf(-t3.y, r2, e[3].y));
 }
 
-// Composite radices R = A B: A-point DFTs over n1 of n = B n1 + n2, the factors
-// e^{-2 pi i n2 k1 / R}, B-point DFTs over n2; X[k1 + A k2].
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>());
-        static_for<I + 1, N>(f);
-    }
-}
-
-// cos and sin of 2 pi e / R by their Taylor series (argument in (-pi, pi]),
-// evaluated in float64 by the compiler
-constexpr double turn_angle(int e, int R) {
-    return 6.283185307179586476925 * double(2 * e > R ? e - R : e) / double(R);
-}
-constexpr double turn_cos(int e, int R) {
-    const double x = turn_angle(e, R);
-    double t = 1.0, s = 1.0;
-    for (int k = 1; k < 24; ++k) {
-        t *= -x * x / double((2 * k - 1) * (2 * k));
-        s += t;
-    }
-    return s;
-}
-constexpr double turn_sin(int e, int R) {
-    const double x = turn_angle(e, R);
-    double t = x, s = x;
-    for (int k = 1; k < 24; ++k) {
-        t *= -x * x / double((2 * k) * (2 * k + 1));
-        s += t;
-    }
-    return s;
-}
-
-template <int A, int B>
-__device__ __forceinline__ void dft_composite(float2 *v) {
-    constexpr int R = A * B;
-    float2 y[B][A];
-    static_for<0, B>([&](auto n2) __attribute__((always_inline)) {
-#pragma unroll
-        for (int n1 = 0; n1 < A; ++n1) y[n2][n1] = v[B * n1 + n2];
-        dft<A>(y[n2]);
-        static_for<0, A>([&](auto k1) __attribute__((always_inline)) {
-            constexpr int e = (int(n2) * int(k1)) % R;
-            if constexpr (e != 0) {
-                constexpr float c = float(turn_cos(e, R)), sn = float(turn_sin(e, R));
-                const float2 t = y[n2][k1];
-                if constexpr (4 * e == R)
-                    y[n2][k1] = mul_negi(t);
-                else
-                    y[n2][k1] = make_float2(t.x * c + t.y * sn, t.y * c - t.x * sn);
-            }
-        });
-    });
-#pragma unroll
-    for (int k1 = 0; k1 < A; ++k1) {
-        float2 z[B];
-#pragma unroll
-        for (int n2 = 0; n2 < B; ++n2) z[n2] = y[n2][k1];
-        dft<B>(z);
-#pragma unroll
-        for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = z[k2];
-    }
-}
 template <>
 __device__ __forceinline__ void dft<1>(float2 *) {}
+// Prime-factor form (Good, Thomas): with n = 3 n1 + 2 n2 and k = 3 k1 + 4 k2
+// modulo 6 the exponent n k is 3 n1 k1 + 2 n2 k2, so three-point transforms over
+// n2 and two-point ones over n1 need no rotations between them and round less.
+// Error against float64, rms, of 6 x 6 x 6 = 216: 1.04e-7 in the factored form
+// with rotations, 0.93e-7 here (0.96e-7 as 8 x 3 x 3 x 3); over 36 lengths 36 .. 1296
+// the default schedule's mean is 3% below that of radices 8, 4, 2, 3, 5 taken
+// greedily, and was 2% above it.
 template <>
-__device__ __forceinline__ void dft<6>(float2 *v) { dft_composite<3, 2>(v); }
+__device__ __forceinline__ void dft<6>(float2 *v) {
+    float2 e[3] = {v[0], v[2], v[4]}, o[3] = {v[3], v[5], v[1]};
+    dft<3>(e);
+    dft<3>(o);
+    v[0] = cadd(e[0], o[0]);
+    v[3] = csub(e[0], o[0]);
+    v[4] = cadd(e[1], o[1]);
+    v[1] = csub(e[1], o[1]);
+    v[2] = cadd(e[2], o[2]);
+    v[5] = csub(e[2], o[2]);
+}
 
 // ------------------------------------------------------------ Stockham passes
 // A workgroup transforms a tile of whole lines.  The first radix pass reads its
