@@ -850,7 +850,7 @@ int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s
     {
         int tsum = 0;
         for (int ax = 0; ax < p->d; ++ax) tsum += p->T[ax];
-        a.cols = p->grid_cols ? grid_cols_waves(p->n_items, p->M, grids, p->chunk, col != nullptr) : 0;
+        a.cols = p->grid_cols ? grid_cols_waves(p->n_items, p->M, grids, col != nullptr) : 0;
         if (a.cols) a.mfma = 0;
         a.grids_per_wg = a.mfma ? grid_grids_per_wg(grids, p->tile_cells, tsum) : 1;
     }

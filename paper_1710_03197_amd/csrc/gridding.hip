@@ -560,6 +560,15 @@ __global__ __launch_bounds__(256) void k_grid_mfma_multi(const GridArgs *__restr
 // latency and reads (four per two products) and the staging.  Measured, row-tile
 // form -> this: 8 grids of 640 x 640, M = 128000: 72 -> 38 us; 24 grids of 256 x
 // 256, M = 20011: 54 -> 31 us; 24 spirals x 8 coils: 1215 -> 447 us.
+//
+// A work item's batches of 64 samples go round-robin to kColSums running sums,
+// which are added in order at the end: to one wavefront each (NW = 4), or one
+// sum after the other on a single wavefront, which then holds two sets of
+// accumulators (201 registers, two wavefronts a SIMD, where one chain over all
+// batches took 134 and three: 24 spirals x 8 coils 1766 -> 1787 us a pass).  Both
+// forms give the same bits, so a problem's result does not depend on what shares
+// its launch, and chains stay a quarter of the chunk.
+constexpr int kColSums = 4;
 template <int NJ, bool TAB, int NW>
 __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, int gg) {
     constexpr int T = 16, NBLK = 16;
@@ -587,7 +596,7 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     const int g0 = gg * kColGrids;
     const int ng = min(kColGrids, a.grids - g0);
     const int rl = lane & 15, kq = lane >> 4;
-    mfma_f4 acc[NBLK];
+    mfma_f4 acc[NBLK], tot[NW == 1 ? NBLK : 1];
 #pragma unroll
     for (int q = 0; q < NBLK; ++q) acc[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
     // trajectory (or window record) and values of this lane's next sample,
@@ -598,9 +607,9 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     bool pvalid = false;
     int cursor = 0;
     auto fetch = [&](int b) {
-        const int s_idx = b + wave * 64 + lane;
+        const int s_idx = b + lane;
         pvalid = s_idx < n;
-        const int sg = batch_segment(seg_pre, nseg, cursor, f0 + b + wave * 64, 64, f0 + s_idx);
+        const int sg = batch_segment(seg_pre, nseg, cursor, f0 + b, 64, f0 + s_idx);
         if (pvalid) {
             const int64_t i = seg_lo[sg] + (f0 + s_idx - seg_pre[sg]);
             if constexpr (TAB) {
@@ -614,8 +623,13 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
             for (int q = 0; q < kColGrids; ++q) pv[q] = q < ng ? y[int64_t(q) * a.M] : make_float2(0.f, 0.f);
         }
     };
-    fetch(0);
-    for (int b0 = 0; b0 < n; b0 += 64 * NW) {
+    int b0 = wave * 64;  // first sample of the wavefront's batch
+    if constexpr (NW == 1) {
+#pragma unroll
+        for (int q = 0; q < NBLK; ++q) tot[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
+    }
+    fetch(b0);
+    while (b0 < n) {
         {
             float4 *z = reinterpret_cast<float4 *>(rec);
             for (int e = lane; e < 16 * RS; e += 64) z[e] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -666,7 +680,15 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
                 if ((bm[0] >> b) & 1u) mk |= bm[1] << (4 * b);
         }
         smask[lane] = mk;
-        if (b0 + 64 * NW < n) fetch(b0 + 64 * NW);
+        // the next batch of this running sum, else (one wavefront) the first of the next
+        int next = b0 + 64 * kColSums;
+        const bool flush = NW == 1 && next >= n;
+        if (flush) {
+            next = (b0 & (64 * kColSums - 1)) + 64;
+            if (next >= 64 * kColSums) next = n;
+            cursor = 0;
+        }
+        if (next < n) fetch(next);
         group_sync(64);
         // ---- walk: lane l < 16 looks at samples 4 l .. 4 l + 3.  Two blocks
         // side by side at a time (they share the values and the row weights,
@@ -697,6 +719,16 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
                 acc[q + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * d1, w1, acc[q + 1], 0, 0, 0);
             }
         }
+        if constexpr (NW == 1) {
+            if (flush) {
+#pragma unroll
+                for (int q = 0; q < NBLK; ++q) {
+                    tot[q] += acc[q];
+                    acc[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+        }
+        b0 = next;
         group_sync(64);
     }
     // ---- write the tile.  D[i][j] of block q sits in lane j + 16 (i / 4),
@@ -723,7 +755,7 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     };
     if constexpr (NW == 1) {
 #pragma unroll
-        for (int q = 0; q < NBLK; ++q) store_block(q, acc[q]);
+        for (int q = 0; q < NBLK; ++q) store_block(q, tot[q]);
     } else {
         // the wavefronts' blocks are summed in wave order through LDS, half of
         // them at a time; wavefront w sums and stores every NW-th block

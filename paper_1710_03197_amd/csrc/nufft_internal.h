@@ -311,19 +311,15 @@ struct GridArgs {
 // needs about 5 us for 64 samples, most of it LDS latency, so four share an item
 // (8 grids of 640 x 640: 92 us with one, 38 with four) until the items alone
 // fill the chip, as in a multi-problem launch (24 problems: 627 us with four,
-// 447 with one).  One wavefront adds all of an item's samples in one chain, so
-// it is kept to chunks whose rounding then stays at the row-tile form's (adjoint
-// error against float64 1.4e-7 at 1536 samples a chunk, 1.2e-7 at 512 and for
-// the row-tile form).
+// 465 with one).  Both give the same bits.
 constexpr int kColGrids = 8;  // grids that fill a product's 16 columns
 constexpr int kGridColsMin = 3;
 constexpr int64_t kGridColsWork = 32768;
 constexpr int64_t kGridColsItems = 12288;  // 12 wavefronts a CU, four deep
-constexpr int kGridColsChain = 512;        // samples one wavefront may sum in a chain
-inline int grid_cols_waves(int64_t items, int64_t M, int grids, int chunk, bool multi) {
+inline int grid_cols_waves(int64_t items, int64_t M, int grids, bool multi) {
     if (grids < kGridColsMin || M * grids < kGridColsWork) return 0;
     const bool filled = multi || items * ((grids + kColGrids - 1) / kColGrids) >= kGridColsItems;
-    return filled && chunk <= kGridColsChain ? 1 : 4;
+    return filled ? 1 : 4;
 }
 // Grids per workgroup of the row-tile matrix-core gridding: the window weights
 // are staged once for all of them (coils and batch entries share the
