@@ -558,20 +558,19 @@ __global__ __launch_bounds__(256) void k_grid_mfma_multi(const GridArgs *__restr
 // over the tile, taps outside it to a discard slot, the set of blocks reached),
 // then block by block the groups of four samples that reach it.  Bound by LDS
 // latency and reads (four per two products) and the staging.  Measured, row-tile
-// form -> this: 8 grids of 640 x 640, M = 128000: 72 -> 38 us; 24 grids of 256 x
-// 256, M = 20011: 54 -> 31 us; 24 spirals x 8 coils: 1215 -> 447 us.
+// form -> this: 8 grids of 640 x 640, M = 128000: 72 -> 30 us; 24 grids of 256 x
+// 256, M = 20011: 54 -> 28 us; 24 spirals x 8 coils: 1215 -> 450 us.
 //
-// A work item's batches of 64 samples go round-robin to kColSums running sums,
-// which are added in order at the end: to one wavefront each (NW = 4), or one
-// sum after the other on a single wavefront, which then holds two sets of
-// accumulators (201 registers, two wavefronts a SIMD, where one chain over all
-// batches took 134 and three: 24 spirals x 8 coils 1766 -> 1787 us a pass).  Both
-// forms give the same bits, so a problem's result does not depend on what shares
-// its launch, and chains stay a quarter of the chunk.
-constexpr int kColSums = 4;
+// A batch's products with a block are one chain from zero, and an item's chains
+// are added in batch order.  NW = 1: one wavefront does all of it.  NW = 4: four
+// wavefronts stage a batch each and then walk all four, each for its own row of
+// blocks.  Both give the same bits, so a problem's result does not depend on what
+// shares its launch, and chains of 64 samples round less than the one chain over
+// all of a wavefront's batches that they replace (adjoint of 24 spirals x 8 coils
+// against float64 1.13e-7 -> 1.02e-7; 1768 -> 1766 us a pass).
 template <int NJ, bool TAB, int NW>
 __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, int gg) {
-    constexpr int T = 16, NBLK = 16;
+    constexpr int T = 16, ROWS = 4 / NW;
     constexpr int RS = 2 * T + 1;            // weights of a sample, then the discard slot (odd)
     constexpr int VS = 2 * kColGrids + 1;    // its values (odd)
     extern __shared__ float col_lds[];
@@ -582,9 +581,9 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     const int J = a.geo.J;
     const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    float *rec = col_lds + wave * 64 * (RS + VS + 1);                 // [64][RS]
-    float *val = rec + 64 * RS;                                       // [64][VS]
-    unsigned *smask = reinterpret_cast<unsigned *>(val + 64 * VS);    // [64]
+    float *rec = col_lds;                                             // [NW][64][RS]
+    float *val = rec + NW * 64 * RS;                           // [NW][64][VS]
+    unsigned *smask = reinterpret_cast<unsigned *>(val + NW * 64 * VS);  // [NW][64]
     const int t0 = it.tile / a.nt[1];
     const int t1 = it.tile - t0 * a.nt[1];
     const int base[2] = {tile_base(t0, a.geo.K[0], T, a.nt[0]), tile_base(t1, a.geo.K[1], T, a.nt[1])};
@@ -596,9 +595,9 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
     const int g0 = gg * kColGrids;
     const int ng = min(kColGrids, a.grids - g0);
     const int rl = lane & 15, kq = lane >> 4;
-    mfma_f4 acc[NBLK], tot[NW == 1 ? NBLK : 1];
+    mfma_f4 tot[ROWS][4];  // the wavefront's blocks
 #pragma unroll
-    for (int q = 0; q < NBLK; ++q) acc[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < 4 * ROWS; ++q) tot[q / 4][q % 4] = mfma_f4{0.f, 0.f, 0.f, 0.f};
     // trajectory (or window record) and values of this lane's next sample,
     // loaded one batch ahead
     float pom[TAB ? 1 : 2];
@@ -623,15 +622,10 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
             for (int q = 0; q < kColGrids; ++q) pv[q] = q < ng ? y[int64_t(q) * a.M] : make_float2(0.f, 0.f);
         }
     };
-    int b0 = wave * 64;  // first sample of the wavefront's batch
-    if constexpr (NW == 1) {
-#pragma unroll
-        for (int q = 0; q < NBLK; ++q) tot[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
-    }
-    fetch(b0);
-    while (b0 < n) {
+    fetch(wave * 64);
+    for (int b0 = 0; b0 < n; b0 += NW * 64) {
         {
-            float4 *z = reinterpret_cast<float4 *>(rec);
+            float4 *z = reinterpret_cast<float4 *>(rec + wave * 64 * RS);
             for (int e = lane; e < 16 * RS; e += 64) z[e] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
         group_sync(64);
@@ -643,11 +637,11 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
 #pragma unroll
         for (int q = 0; q < kColGrids; ++q) {
             const float2 v = pvalid ? (a.geo.minmax ? cmulcj(ph, pv[q]) : pv[q]) : make_float2(0.f, 0.f);
-            val[lane * VS + 2 * q] = v.x;
-            val[lane * VS + 2 * q + 1] = v.y;
+            val[int(threadIdx.x) * VS + 2 * q] = v.x;
+            val[int(threadIdx.x) * VS + 2 * q + 1] = v.y;
         }
         if (pvalid) {
-            float *my = rec + lane * RS;
+            float *my = rec + int(threadIdx.x) * RS;
             int kwa[2];
             float wva[2][NJ];
             if constexpr (TAB)
@@ -679,57 +673,55 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
             for (int b = 0; b < 4; ++b)
                 if ((bm[0] >> b) & 1u) mk |= bm[1] << (4 * b);
         }
-        smask[lane] = mk;
-        // the next batch of this running sum, else (one wavefront) the first of the next
-        int next = b0 + 64 * kColSums;
-        const bool flush = NW == 1 && next >= n;
-        if (flush) {
-            next = (b0 & (64 * kColSums - 1)) + 64;
-            if (next >= 64 * kColSums) next = n;
-            cursor = 0;
-        }
-        if (next < n) fetch(next);
-        group_sync(64);
-        // ---- walk: lane l < 16 looks at samples 4 l .. 4 l + 3.  Two blocks
-        // side by side at a time (they share the values and the row weights,
-        // and their products are independent), two groups of samples per step.
+        smask[threadIdx.x] = mk;
+        if (b0 + NW * 64 < n) fetch(b0 + NW * 64 + wave * 64);
+        group_sync(64 * NW);
+        // ---- walk: lane l looks at samples 4 l .. 4 l + 3, so 16 bits of a
+        // ballot are a batch.  Two blocks side by side at a time (they share the
+        // values and the row weights, and their products are independent), two
+        // groups of samples per step; a batch's products are one chain, added to
+        // the block's total.
         unsigned gm = 0;
-        if (lane < 16) {
+        if (lane < 16 * NW) {
             const uint4 m4 = reinterpret_cast<const uint4 *>(smask)[lane];
             gm = m4.x | m4.y | m4.z | m4.w;
         }
 #pragma unroll
-        for (int q = 0; q < NBLK; q += 2) {
-            const int a0 = 4 * (q / 4) + (rl >> 2);
-            const int a1 = T + 4 * (q % 4) + (rl & 3);
-            uint64_t act = __ballot(((gm >> q) & 3u) != 0u);
-            while (act) {
-                const int i0 = int(__builtin_ctzll(act));
-                act &= act - 1;
-                const bool two = act != 0;
-                const int i1 = two ? int(__builtin_ctzll(act)) : i0;
-                act &= act - 1;
-                const float *s0 = rec + (4 * i0 + kq) * RS, *s1 = rec + (4 * i1 + kq) * RS;
-                const float v0 = val[(4 * i0 + kq) * VS + rl], v1 = val[(4 * i1 + kq) * VS + rl];
-                const float r0 = s0[a0], c0 = s0[a1], d0 = s0[a1 + 4], r1 = s1[a0], c1 = s1[a1], d1 = s1[a1 + 4];
-                const float w1 = two ? v1 : 0.f;
-                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(r0 * c0, v0, acc[q], 0, 0, 0);
-                acc[q + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(r0 * d0, v0, acc[q + 1], 0, 0, 0);
-                acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * c1, w1, acc[q], 0, 0, 0);
-                acc[q + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * d1, w1, acc[q + 1], 0, 0, 0);
-            }
-        }
-        if constexpr (NW == 1) {
-            if (flush) {
+        for (int r = 0; r < ROWS; ++r) {
+            const int row = wave * ROWS + r;
+            const int a0 = 4 * row + (rl >> 2);
 #pragma unroll
-                for (int q = 0; q < NBLK; ++q) {
-                    tot[q] += acc[q];
-                    acc[q] = mfma_f4{0.f, 0.f, 0.f, 0.f};
+            for (int q = 0; q < 4; q += 2) {
+                const int a1 = T + 4 * q + (rl & 3);
+                const uint64_t reached = __ballot(((gm >> (4 * row + q)) & 3u) != 0u);
+                for (int w = 0; w < NW; ++w) {
+                    uint64_t act = NW == 1 ? reached : reached & (uint64_t(0xffff) << (16 * w));
+                    if (!act) continue;
+                    mfma_f4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
+                    do {
+                        const int i0 = int(__builtin_ctzll(act));
+                        act &= act - 1;
+                        const bool two = act != 0;
+                        const int i1 = two ? int(__builtin_ctzll(act)) : i0;
+                        act &= act - 1;
+                        const float *s0 = rec + (4 * i0 + kq) * RS, *s1 = rec + (4 * i1 + kq) * RS;
+                        const float v0 = val[(4 * i0 + kq) * VS + rl], v1 = val[(4 * i1 + kq) * VS + rl];
+                        const float r0 = s0[a0], x0 = s0[a1], y0 = s0[a1 + 4], r1 = s1[a0], x1 = s1[a1], y1 = s1[a1 + 4];
+                        // (left alone, the compiler waits for the first group's products
+                        // before it loads the second's values: 1774 us against 1766)
+                        __builtin_amdgcn_sched_barrier(0);
+                        const float w1 = two ? v1 : 0.f;
+                        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(r0 * x0, v0, c0, 0, 0, 0);
+                        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(r0 * y0, v0, c1, 0, 0, 0);
+                        c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * x1, w1, c0, 0, 0, 0);
+                        c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(r1 * y1, w1, c1, 0, 0, 0);
+                    } while (act);
+                    tot[r][q] += c0;
+                    tot[r][q + 1] += c1;
                 }
             }
         }
-        b0 = next;
-        group_sync(64);
+        group_sync(64 * NW);
     }
     // ---- write the tile.  D[i][j] of block q sits in lane j + 16 (i / 4),
     // register i % 4: the lane holds part j & 1 of grid j / 2 at row x0 = 4
@@ -753,27 +745,10 @@ __device__ __forceinline__ void grid_cols_body(const GridArgs &a, int64_t item, 
         const int64_t idx = first + x0 * pitch + x1;
         if (g - g0 < ng && (to_partial || (x0 < width[0] && x1 < width[1]))) *reinterpret_cast<float4 *>(dst + idx) = cells;
     };
-    if constexpr (NW == 1) {
 #pragma unroll
-        for (int q = 0; q < NBLK; ++q) store_block(q, tot[q]);
-    } else {
-        // the wavefronts' blocks are summed in wave order through LDS, half of
-        // them at a time; wavefront w sums and stores every NW-th block
-        constexpr int HB = NBLK / 2;
-        mfma_f4 *red = reinterpret_cast<mfma_f4 *>(col_lds);  // [NW][HB][64]
+    for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            __syncthreads();  // the staging area, or the previous half, is done with
-#pragma unroll
-            for (int q = 0; q < HB; ++q) red[(wave * HB + q) * 64 + lane] = acc[h * HB + q];
-            __syncthreads();
-            for (int q = wave; q < HB; q += NW) {
-                mfma_f4 sum = red[q * 64 + lane];
-#pragma unroll
-                for (int w = 1; w < NW; ++w) sum += red[(w * HB + q) * 64 + lane];
-                store_block(h * HB + q, sum);
-            }
-        }
+        for (int q = 0; q < 4; ++q) store_block(4 * (wave * ROWS + r) + q, tot[r][q]);
     }
 }
 
