@@ -577,8 +577,12 @@ struct Emitted {
     ReduceArgs reduce{};
     PermuteJob permute{};
 };
+// col_groups, gather_grids: the work of the sample kernels over all problems of
+// the call, by which the recorded launches choose their forms.
 struct Collector {
     std::vector<Emitted> out;
+    int64_t col_groups = 0;
+    int64_t gather_grids = 0;
     Emitted &add(int slot, int kind) {
         out.emplace_back();
         out.back().slot = slot;
@@ -771,6 +775,13 @@ int run_shfh(nufft_plan_s *p, const FftGeom &f, const float2 *h, int B, float2 *
     return NUFFT_OK;
 }
 
+// Work of a call's sample kernels: (item, grid) pairs of the staged gather, and
+// (item, group of eight grids) pairs of the column gridding.
+int64_t gather_grids(const nufft_plan_s *p, int grids) { return p->staged_interp ? p->n_iitems * grids : 0; }
+int64_t col_groups(const nufft_plan_s *p, int grids) {
+    return p->grid_cols && takes_grid_cols(p->M, grids) ? p->n_items * ((grids + kColGrids - 1) / kColGrids) : 0;
+}
+
 // sorted: the samples are left in the plan's sorted order.
 int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s, Collector *col = nullptr,
           bool sorted = false) {
@@ -787,8 +798,7 @@ int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s,
     a.items = p->staged_interp ? p->iitems : nullptr;
     a.n_items = p->n_iitems;
     a.merge = p->interp_merge;
-    // (in a multi-problem launch the other problems fill the chip)
-    a.grids_per_wg = a.items && !col ? interp_grids_per_wg(p->d, a.n_items, grids) : grids;
+    a.grids_per_wg = a.items ? interp_grids_per_wg(p->d, col ? col->gather_grids : gather_grids(p, grids), grids) : grids;
     for (int ax = 0; ax < p->d; ++ax) {
         a.T[ax] = p->T[ax];
         a.nt[ax] = p->nt[ax];
@@ -850,7 +860,7 @@ int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s
     {
         int tsum = 0;
         for (int ax = 0; ax < p->d; ++ax) tsum += p->T[ax];
-        a.cols = p->grid_cols ? grid_cols_waves(p->n_items, p->M, grids, col != nullptr) : 0;
+        a.cols = p->grid_cols ? grid_cols_waves(col ? col->col_groups : col_groups(p, grids), p->M, grids) : 0;
         if (a.cols) a.mfma = 0;
         a.grids_per_wg = a.mfma ? grid_grids_per_wg(grids, p->tile_cells, tsum) : 1;
     }
@@ -1004,7 +1014,8 @@ void stage_blocks(const Emitted &em, int job, int threads, std::vector<int4> &ou
             const InterpArgs &a = em.interp;
             if (a.M == 0) break;
             const int64_t n = a.items ? a.n_items : (a.M + 255) / 256;
-            for (int64_t b = 0; b < n; ++b) out.push_back(make_int4(job, int(b), 0, 0));
+            for (int g = 0; g * a.grids_per_wg < a.grids; ++g)
+                for (int64_t b = 0; b < n; ++b) out.push_back(make_int4(job, int(b), g, 0));
             break;
         }
         case kStGrid: {
@@ -1055,6 +1066,16 @@ int64_t stage_key(const Emitted &em) {
 int build_call(nufft_multi_s *m, bool forward, const void *const *in, void *const *out, MultiCall &mc) {
     const size_t P = m->plans.size();
     std::vector<Collector> cols(P);
+    int64_t groups = 0, gathers = 0;
+    for (nufft_plan_s *pl : m->plans) {
+        const int C = pl->coil_mode ? pl->C : 1;
+        groups += col_groups(pl, C);
+        gathers += gather_grids(pl, C);
+    }
+    for (Collector &c : cols) {
+        c.col_groups = groups;
+        c.gather_grids = gathers;
+    }
     for (size_t p = 0; p < P; ++p) {
         nufft_plan_s *pl = m->plans[p];
         const int C = pl->coil_mode ? pl->C : 1;

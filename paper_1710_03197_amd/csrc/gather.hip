@@ -233,7 +233,7 @@ template <int J, int DIM>
 __global__ __launch_bounds__(interp_threads(DIM)) void k_interp_multi(const InterpArgs *__restrict__ jobs,
                                                      const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
-    interp_body<J, DIM>(jobs[b.x], b.y, 0);
+    interp_body<J, DIM>(jobs[b.x], b.y, b.z);
 }
 
 // Gather straight from the grid (L1/L2), one thread per sorted sample: used

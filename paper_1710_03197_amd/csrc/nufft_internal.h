@@ -242,9 +242,10 @@ hipError_t launch_interp(const InterpArgs &a, hipStream_t s);
 // grid is a round trip to memory between two barriers.  Measured, all -> split:
 // 24 grids of 256 x 256 with 130 items 63.8 -> 20 us; 8 grids of 640 x 640 with
 // 720 items 31.9 -> 25.4 us (4 workgroups per item).
-inline int interp_grids_per_wg(int d, int64_t items, int grids) {
+// work: the (item, grid) pairs of the launch, over all its problems.
+inline int interp_grids_per_wg(int d, int64_t work, int grids) {
     const int64_t groups = 2048 * 256 / interp_threads(d);
-    return int(std::max<int64_t>(1, std::min<int64_t>(grids, items * grids / groups)));
+    return int(std::max<int64_t>(1, std::min<int64_t>(grids, work / groups)));
 }
 // Elements of a gather item's LDS region: the tiles (merge of them along the
 // last axis) plus the J - 1 halo, the last axis made odd.
@@ -309,17 +310,18 @@ struct GridArgs {
 // products per grid: it pays from three grids.  Calls of few samples stay with
 // the row-tile form: both are launch and latency bound there.  One wavefront
 // needs about 5 us for 64 samples, most of it LDS latency, so four share an item
-// (8 grids of 640 x 640: 92 us with one, 38 with four) until the items alone
-// fill the chip, as in a multi-problem launch (24 problems: 627 us with four,
-// 465 with one).  Both give the same bits.
+// until the launch (groups: its (item, group of kColGrids grids) pairs over all
+// problems) fills the chip several times over; both give the same bits.  Adjoint
+// of the first P of 24 spirals x 8 coils, four -> one: P = 1 (1957 groups) 96 ->
+// 133 us, 2 (3900) 151 -> 168, 4 (6784) 230 -> 223, 8 398 -> 351, 24 1086 -> 937; 24 grids of
+// 640 x 640 (4800 groups), 500 samples 73 -> 73, 64000 samples 130 -> 151.
 constexpr int kColGrids = 8;  // grids that fill a product's 16 columns
 constexpr int kGridColsMin = 3;
 constexpr int64_t kGridColsWork = 32768;
-constexpr int64_t kGridColsItems = 12288;  // 12 wavefronts a CU, four deep
-inline int grid_cols_waves(int64_t items, int64_t M, int grids, bool multi) {
-    if (grids < kGridColsMin || M * grids < kGridColsWork) return 0;
-    const bool filled = multi || items * ((grids + kColGrids - 1) / kColGrids) >= kGridColsItems;
-    return filled ? 1 : 4;
+constexpr int64_t kGridColsFilled = 6144;
+inline bool takes_grid_cols(int64_t M, int grids) { return grids >= kGridColsMin && M * grids >= kGridColsWork; }
+inline int grid_cols_waves(int64_t groups, int64_t M, int grids) {
+    return !takes_grid_cols(M, grids) ? 0 : groups >= kGridColsFilled ? 1 : 4;
 }
 // Grids per workgroup of the row-tile matrix-core gridding: the window weights
 // are staged once for all of them (coils and batch entries share the

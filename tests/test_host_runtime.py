@@ -255,3 +255,30 @@ def test_default_table_gives_way_to_the_workspace(host, option, status):
     log = host.call("nufft_adjoint_batched", p, 8, _buf(1), _buf(2), None)
     assert [(e["table"], e["live"]) for e in log if e["what"] == "grid"] == [("01"[option], "1")]
     host.call("nufft_destroy", p)
+
+
+# ---- which gridding and gather forms a call takes
+def test_multi_problem_forms_follow_the_whole_launch(host):
+    """One and two problems take the forms of their single plans; many take one
+    wavefront a gridding item and all coils in a gather workgroup.  Row-tile or
+    column gridding is each problem's own choice in every launch."""
+    om = np.full((5000, 2), 0.5, np.float32)
+    big, small = ((256, 256), (512, 512), 6, om, 8, {}), ((64, 64), (128, 128), 6, om[:2000], 8, {})
+    single, _ = host.plan((256, 256), (512, 512), 6, om)
+    gather = [int(e["grids_per_wg"]) for e in host.call("nufft_forward_batched", single, 8, _buf(1), _buf(2), None)
+              if e["what"] == "interp"]
+    host.call("nufft_destroy", single)
+    for problems, waves in (([big], 4), ([big, small], 4), ([big] * 2, 4), ([big] * 16, 1), ([small] + [big] * 16, 1)):
+        m = host.multi(problems)
+        ptrs = (ctypes.c_void_p * len(problems))(*[_buf(k + 1) for k in range(len(problems))])
+        adj = [e for e in host.call("nufft_multi_adjoint", m, ptrs, ptrs, None) if e["what"] == "grid_multi"]
+        fwd = [e for e in host.call("nufft_multi_forward", m, ptrs, ptrs, None) if e["what"] == "interp_multi"]
+        assert {int(e["cols"]) for e in adj} == ({0, waves} if small in problems else {waves})
+        if problems == [big]:
+            assert int(fwd[0]["grids_per_wg"]) == gather[0]
+        host.call("nufft_multi_destroy", m)
+    m = host.multi([((256, 256), (512, 512), 6, np.full((40000, 2), 0.5, np.float32), 8, {})] * 40)
+    ptrs = (ctypes.c_void_p * 40)(*[_buf(k + 1) for k in range(40)])
+    fwd = [e for e in host.call("nufft_multi_forward", m, ptrs, ptrs, None) if e["what"] == "interp_multi"]
+    assert fwd[0]["grids_per_wg"] == "8"
+    host.call("nufft_multi_destroy", m)
