@@ -779,7 +779,7 @@ int run_shfh(nufft_plan_s *p, const FftGeom &f, const float2 *h, int B, float2 *
 // (item, group of eight grids) pairs of the column gridding.
 int64_t gather_grids(const nufft_plan_s *p, int grids) { return p->staged_interp ? p->n_iitems * grids : 0; }
 int64_t col_groups(const nufft_plan_s *p, int grids) {
-    return p->grid_cols && takes_grid_cols(p->M, grids) ? p->n_items * ((grids + kColGrids - 1) / kColGrids) : 0;
+    return p->grid_cols && takes_grid_cols(p->n_items, grids) ? p->n_items * ((grids + kColGrids - 1) / kColGrids) : 0;
 }
 
 // sorted: the samples are left in the plan's sorted order.
@@ -860,7 +860,8 @@ int run_vh(nufft_plan_s *p, const float2 *y, int grids, float2 *h, hipStream_t s
     {
         int tsum = 0;
         for (int ax = 0; ax < p->d; ++ax) tsum += p->T[ax];
-        a.cols = p->grid_cols ? grid_cols_waves(col ? col->col_groups : col_groups(p, grids), p->M, grids) : 0;
+        const int64_t groups = col_groups(p, grids);
+        a.cols = groups ? grid_cols_waves(col ? col->col_groups : groups) : 0;
         if (a.cols) a.mfma = 0;
         a.grids_per_wg = a.mfma ? grid_grids_per_wg(grids, p->tile_cells, tsum) : 1;
     }

@@ -305,24 +305,31 @@ struct GridArgs {
     int grids_per_wg;     // row-tile matrix-core gridding: grids one workgroup grids together (1, 2, 4)
     int grid_waves;       // block gridding: wavefronts per work item (1 or 4)
 };
-// Wavefronts per work item of the column form, 0 where the row-tile form is
-// taken.  A product costs the same for one to eight grids, the row-tile form two
-// products per grid: it pays from three grids.  Calls of few samples stay with
-// the row-tile form: both are launch and latency bound there.  One wavefront
-// needs about 5 us for 64 samples, most of it LDS latency, so four share an item
-// until the launch (groups: its (item, group of kColGrids grids) pairs over all
-// problems) fills the chip several times over; both give the same bits.  Adjoint
-// of the first P of 24 spirals x 8 coils, four -> one: P = 1 (1957 groups) 96 ->
-// 133 us, 2 (3900) 151 -> 168, 4 (6784) 230 -> 223, 8 398 -> 351, 24 1086 -> 937; 24 grids of
-// 640 x 640 (4800 groups), 500 samples 73 -> 73, 64000 samples 130 -> 151.
+// The column form or the row-tile form: by the problem alone, since the two round
+// differently and a problem's bits shall not depend on what shares its launch.
+// A workgroup of the column form grids eight grids in 1.1 to 1.3 times the time
+// the row-tile form takes for four, once either fills the chip; below that
+// both are chains of latencies, and the row-tile form's is the shorter.  Gridding
+// in us, row-tile -> column form, by (image, samples, grids) and row-tile
+// workgroups: (320, 64000, 3) 1690: 21 -> 24; (320, 64000, 8) 3380: 39 -> 25; (320,
+// 500, 8) 3200: 23 -> 14; (128, 64000, 8) 838: 22 -> 25; (128, 64000, 24) 2514: 57 ->
+// 41; (128, 4000, 24) 1560: 25 -> 25; (64, 16000, 24) 672: 22 -> 26; (64, 64000, 24)
+// 1824: 56 -> 39; (32, 4000, 24) 168: 14 -> 22.
 constexpr int kColGrids = 8;  // grids that fill a product's 16 columns
-constexpr int kGridColsMin = 3;
-constexpr int64_t kGridColsWork = 32768;
-constexpr int64_t kGridColsFilled = 6144;
-inline bool takes_grid_cols(int64_t M, int grids) { return grids >= kGridColsMin && M * grids >= kGridColsWork; }
-inline int grid_cols_waves(int64_t groups, int64_t M, int grids) {
-    return !takes_grid_cols(M, grids) ? 0 : groups >= kGridColsFilled ? 1 : 4;
+constexpr int kGridColsMin = 5;            // grids: two groups of the row-tile form or more
+constexpr int64_t kGridColsGroups = 1024;  // row-tile workgroups the chip holds at once
+inline bool takes_grid_cols(int64_t items, int grids) {
+    return grids >= kGridColsMin && items * ((grids + 3) / 4) >= kGridColsGroups;
 }
+// Its wavefronts per work item, the same bits either way.  Four share an item's
+// batches until the launch (groups: its (item, group of kColGrids grids) pairs
+// over all problems) fills the chip several times over; then one wavefront an
+// item, whose neighbours hide its latencies.  Adjoint of the first P of 24
+// spirals x 8 coils, four -> one: P = 1 (1957 groups) 96 -> 133 us, 2 (3900) 151
+// -> 168, 4 (6784) 230 -> 223, 8 398 -> 351, 24 1086 -> 937; 24 grids of 640 x 640 (4800
+// groups), 500 samples 73 -> 73, 64000 samples 130 -> 151.
+constexpr int64_t kGridColsFilled = 6144;
+inline int grid_cols_waves(int64_t groups) { return groups >= kGridColsFilled ? 1 : 4; }
 // Grids per workgroup of the row-tile matrix-core gridding: the window weights
 // are staged once for all of them (coils and batch entries share the
 // trajectory); four at most, at most eight accumulator blocks per lane, and

@@ -1,5 +1,5 @@
 """Multi-problem launches at sizes where the gridding takes the grids as matrix
-columns (three or more coils, 32768 samples times coils and more): each
+columns, with four wavefronts per work item or, in full launches, one: each
 problem's results are bit for bit those of its own single plan, whatever shares
 the launch, and match the FP64 oracle."""
 import numpy as np
@@ -19,14 +19,14 @@ def dev():
     return torch.device("cuda:0")
 
 
-# N, coils, samples, options.  Work items from part of a batch of 64 to 32 batches (the
-# gridding's four running sums hold 0 to 8 batches each), one and two groups of
-# eight grids, tiles cut unevenly, on-the-fly windows, and one problem that
-# stays with the row-tile form.
-PROBLEMS = [((64, 64), 8, 20000, {}),
-            ((50, 90), 3, 15000, dict(grid_chunk=2048)),
-            ((48, 48), 9, 9000, dict(grid_chunk=64, weight_table=-1)),
-            ((128, 128), 8, 30000, dict(grid_chunk=1536, presort=1, fuse_reduce=2)),
+# N, coils, samples, options.  Five coils and more and 1024 workgroups of four grids
+# and more: work items from part of a batch of 64 samples to 32 batches, one and
+# two groups of eight grids, the last one partly filled, tiles cut unevenly,
+# on-the-fly windows; and one problem that stays with the row-tile form.
+PROBLEMS = [((192, 160), 8, 40000, {}),
+            ((100, 180), 13, 30000, dict(grid_chunk=2048)),
+            ((96, 96), 9, 20000, dict(grid_chunk=64, weight_table=-1)),
+            ((256, 256), 8, 30000, dict(grid_chunk=1536, presort=1, fuse_reduce=2)),
             ((32, 32), 2, 5000, {})]
 
 

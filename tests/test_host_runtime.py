@@ -258,6 +258,27 @@ def test_default_table_gives_way_to_the_workspace(host, option, status):
 
 
 # ---- which gridding and gather forms a call takes
+def _adjoint_cols(host, N, C, M, **options):
+    p, _ = host.plan(N, tuple(2 * n for n in N), 6, np.full((M, 2), 0.5, np.float32), **options)
+    log = host.call("nufft_adjoint_batched", p, C, _buf(1), _buf(2), None)
+    host.call("nufft_destroy", p)
+    return [int(e["cols"]) for e in log if e["what"] == "grid"]
+
+
+@pytest.mark.parametrize("N,grids,cols", [
+    ((320, 320), 3, 0), ((320, 320), 4, 0),     # one group of the row-tile form
+    ((320, 320), 5, 4), ((320, 320), 8, 4),     # 1600 tiles
+    ((128, 128), 8, 0), ((128, 128), 16, 4),    # 256 tiles: 512 and 1024 workgroups of four grids
+    ((64, 64), 24, 0),
+    ((320, 320), 24, 4), ((320, 320), 32, 1),   # 4800 and 6400 groups of eight grids
+])
+def test_column_gridding_is_taken_where_it_is_faster(host, N, grids, cols):
+    """Few grids and few workgroups stay with the row-tile form, whatever the
+    number of samples in a tile's one work item."""
+    for M in (1000, 15000):
+        assert _adjoint_cols(host, N, grids, M) == [cols]
+
+
 def test_multi_problem_forms_follow_the_whole_launch(host):
     """One and two problems take the forms of their single plans; many take one
     wavefront a gridding item and all coils in a gather workgroup.  Row-tile or
