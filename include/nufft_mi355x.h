@@ -124,7 +124,8 @@ int nufft_plan(int d, const int64_t *N, const int64_t *K, int J, int64_t M,
  *                 table, evaluated on the fly; 0: the default (a table for
  *                 Kaiser-Bessel windows of up to 8 taps as long as it takes
  *                 at most 256 MiB, else on the fly); the same weights to the
- *                 bit in every case
+ *                 bit in every case (a 2D interpolation reads the table while
+ *                 it holds at most 32 MiB, and evaluates above that)
  *   fft_radix     radix schedule of the Stockham FFT passes on every axis
  *                 (Section 2.1 "Oversampled FFT"): 0: the fewest passes over
  *                 radices 2 to 6 and 8; 1: radices 4, 8, 2, 3, 5

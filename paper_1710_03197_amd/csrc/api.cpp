@@ -788,6 +788,7 @@ int run_v(nufft_plan_s *p, const float2 *G, int grids, float2 *y, hipStream_t s,
     if (!p->tables) return fail(NUFFT_ERR_OOM, "the plan lost its work lists in a re-bin without memory");
     InterpArgs a{};
     a.geo = p->geom();
+    if (a.geo.wtab && !gather_reads_table(p->d, p->M, a.geo.wtab_stride)) a.geo.wtab = nullptr;
     a.om_sorted = p->om_sorted;
     a.perm = sorted ? p->biota : p->perm;
     a.M = p->M;
@@ -1597,11 +1598,9 @@ int nufft_plan_ex(int d, const int64_t *N, const int64_t *K, int J, int64_t M, c
     // pass: 64 x 64 pair 45.4 -> 39.7 us, 8 coils of 320 x 320 139 -> 131, 3D
     // 96 x 72 x 60 136 -> 120, 3D density compensation 634 -> 554.  Windows wider
     // than 8 taps gain nothing (their gridding evaluates anyway).  The limit is
-    // where it stops paying in 2D, at the size of the last-level cache: radial
-    // pairs on a 1024 x 1024 grid, 3.1 M samples (192 MiB) 251 -> 232 us, 4.2 M (256
-    // MiB) 311 -> 309, 8.4 M (512 MiB) 549 -> 578.  In 3D (256^3 grid) it goes on
-    // paying, 4.2 M samples (320 MiB) 1341 -> 1202 us, 16.8 M (1.25 GiB) 4226 -> 3813;
-    // memory of that order is left to who asks for it.
+    // one of memory, for who did not ask: the gridding goes on gaining above it
+    // (adjoint, radial, 2D 1024 x 1024 grid, 8.4 M samples = 512 MiB 422 -> 411 us; 3D
+    // 256^3, 4.2 M = 320 MiB 928 -> 827), the 2D gather stops sooner (gather_reads_table).
     constexpr int64_t kDefaultTableBytes = int64_t(256) << 20;
     p->use_wtab = p->wtab_asked = opt && opt->weight_table == 1;
     if (!p->use_wtab && !p->minmax && J <= 8 && !(opt && opt->weight_table == -1))

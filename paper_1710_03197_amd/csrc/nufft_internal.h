@@ -208,6 +208,17 @@ struct SampleGeom {
 };
 inline int table_taps(int J) { return J <= 6 ? 6 : J <= 8 ? 8 : 16; }
 inline int table_stride(int d, int J) { return (2 + d * table_taps(J) + 3) & ~3; }
+// Whether the gather reads the table (it gives the same weights).  It visits a
+// sample once, so a 2D record of 64 bytes costs it more than evaluating twelve
+// weights as soon as the records no longer come from cache: J = 6, uniform
+// samples on a 1024 x 1024 grid, on the fly -> table, 0.26 M samples (16 MiB) 14.0 -> 11.7
+// us, 0.52 M (32 MiB) 18.4 -> 17.6, 1.0 M 25.5 -> 28.5, 2.1 M 41 -> 52, 4.2 M 70 -> 115.  In
+// 3D there is more to evaluate and to gather: 256^3 grid, 2.1 M samples (160 MiB)
+// 209 -> 208.
+constexpr int64_t kGatherTableBytes = int64_t(32) << 20;
+inline bool gather_reads_table(int d, int64_t M, int stride) {
+    return d != 2 || M * stride * int64_t(sizeof(float)) <= kGatherTableBytes;
+}
 hipError_t launch_weight_table(const SampleGeom &g, const float *om_sorted, int64_t M, float *out, hipStream_t s);
 
 // Interpolation V: y[g][perm[i]] = sum_taps w * G[g][..] for sorted sample i.

@@ -212,6 +212,7 @@ def test_rebin_without_memory_leaves_no_dangling_lists(host, failures):
     (0, 2, 1000, True), (1, 2, 1000, True), (-1, 2, 1000, False),
     (0, 3, 3355443, True), (0, 3, 3355444, False),  # 80 bytes a sample, 256 MiB
     (1, 3, 3355444, True),
+    (0, 2, 524288, True),
 ])
 def test_window_table_option(host, option, d, M, table):
     """0 takes a table within its limit, 1 always, -1 never."""
@@ -220,6 +221,18 @@ def test_window_table_option(host, option, d, M, table):
     for name, what in (("nufft_forward", "interp"), ("nufft_adjoint", "grid")):
         log = host.call(name, p, _buf(1), _buf(2), None)
         assert [e["table"] for e in log if e["what"] == what] == [str(int(table))]
+    host.call("nufft_destroy", p)
+
+
+@pytest.mark.parametrize("option", [0, 1])
+def test_large_2d_gathers_evaluate_their_windows(host, option):
+    """Above 32 MiB of records the 2D gather is faster on the fly; the gridding,
+    which visits a sample more than once, still reads the table."""
+    p, _ = host.plan((16, 16), (32, 32), 6, np.full((524289, 2), 0.5, np.float32), weight_table=option)
+    log = host.call("nufft_forward", p, _buf(1), _buf(2), None)
+    assert [e["table"] for e in log if e["what"] == "interp"] == ["0"]
+    log = host.call("nufft_adjoint", p, _buf(1), _buf(2), None)
+    assert [e["table"] for e in log if e["what"] == "grid"] == ["1"]
     host.call("nufft_destroy", p)
 
 
