@@ -2069,7 +2069,12 @@ int nufft_toeplitz_plan(nufft_plan_t plan, const float *w_dev, void *stream, nuf
     popt.weight_table = -1;
     st = nufft_plan_ex(d, N2, K2, plan->J, M, plan->om, &popt, stream, &pp);
     if (!st) st = nufft_adjoint(pp, wdev, psf, stream);
-    if (!st) st = ensure_toeplitz_workspace(t.get(), 1);
+    // the workspace of a first application in the plan's coils, where it fits
+    // beside the plan made here; else one grid's, grown by the application
+    if (!st && (!plan->coil_mode || ensure_toeplitz_workspace(t.get(), plan->C) != NUFFT_OK)) {
+        (void)hipGetLastError();
+        st = ensure_toeplitz_workspace(t.get(), 1);
+    }
     if (!st) {
         // P = F(p placed at Delta mod 2N) / prod(2N): the forward passes with
         // image = grid = 2N place the centred p circularly; the scale tables

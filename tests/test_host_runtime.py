@@ -316,3 +316,22 @@ def test_multi_problem_forms_follow_the_whole_launch(host):
     fwd = [e for e in host.call("nufft_multi_forward", m, ptrs, ptrs, None) if e["what"] == "interp_multi"]
     assert fwd[0]["grids_per_wg"] == "8"
     host.call("nufft_multi_destroy", m)
+
+
+# ---- the Toeplitz operator's workspace
+@pytest.mark.parametrize("failures", [0, 1])
+def test_toeplitz_operator_is_made_with_room_for_the_coils(host, failures):
+    """A first application allocates nothing; where the room does not fit, the
+    operator is made with one grid's and grows in the application."""
+    p, _ = host.plan((64, 64), (128, 128), 6, np.full((1000, 2), 0.5, np.float32))
+    maps = np.ones((8, 64, 64), np.complex64)
+    host.call("nufft_set_coils", p, 8, maps.ctypes.data)
+    t = ctypes.c_void_p()
+    host.lib.stub_fail_allocations(8 * 128 * 128 * 8, failures)
+    host.call("nufft_toeplitz_plan", p, None, None, ctypes.byref(t))
+    host.lib.stub_fail_allocations(0, 0)
+    before = host.lib.stub_live_bytes()
+    host.call("nufft_toeplitz_apply", t, 1, _buf(1), _buf(2), None)
+    assert (host.lib.stub_live_bytes() == before) == (failures == 0)
+    host.call("nufft_toeplitz_destroy", t)
+    host.call("nufft_destroy", p)
