@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnufft_mi355x.so")
-SOURCES = ["gather.hip", "gridding.hip", "fft.hip", "points.hip", "kb_host.cpp", "api.cpp"]
+SOURCES = ["gather.hip", "gridding.hip", "fft.hip", "fft_wide.hip", "points.hip", "kb_host.cpp", "api.cpp"]
 HEADERS = ["device.h", "nufft_internal.h"]
 ARCH = os.environ.get("NUFFT_OFFLOAD_ARCH", "gfx950")
 
@@ -30,7 +30,7 @@ FLAGS = [
 
 # per file, after FLAGS: FFT passes that differ only in what they load must give
 # the same bits, so products fuse as the source writes them in every instance
-FILE_FLAGS = {"fft.hip": ["-ffp-contract=on"]}
+FILE_FLAGS = {"fft.hip": ["-ffp-contract=on"], "fft_wide.hip": ["-ffp-contract=on"]}
 
 
 def hipcc() -> str:
@@ -62,6 +62,8 @@ def _stale(obj: str, src: str) -> bool:
     if not os.path.exists(obj):
         return True
     deps = [src, os.path.join(ROOT, "include", "nufft_mi355x.h")] + [os.path.join(CSRC, h) for h in HEADERS]
+    if src.endswith("fft_wide.hip"):
+        deps.append(os.path.join(CSRC, "fft.hip"))
     return any(os.path.getmtime(d) > os.path.getmtime(obj) for d in deps)
 
 

@@ -352,14 +352,6 @@ __device__ __forceinline__ int64_t divmod(int64_t n, int64_t d, int64_t &rem) {
     return q;
 }
 
-// The kernels hold 24 to 75 KB of code each, one branch a radix, and a launch of 7
-// us starts with their fetch.  Each begins on a 64 KiB boundary, so those of up to
-// 64 KiB lie in one translation fragment wherever the others' sizes move them:
-// with 256-byte alignment adding kernels to this file cost the 256 x 256 pair 49.2
-// -> 50.0 us and the 64 x 64 pair 39.4 -> 39.7, with 64 KiB they take 49.5 and 39.2,
-// the Toeplitz operator on 256 x 256 x 8 coils 46.1 -> 45.7.
-#define FFT_KERNEL __global__ __attribute__((aligned(65536))) __launch_bounds__(kFftThreads)
-
 // ------------------------------------------------------------ FFT kernels
 // Dynamic LDS layout of every FFT kernel: [K twiddles][tile].
 template <bool COILS>
@@ -436,14 +428,14 @@ __device__ __forceinline__ void first_pass_body(const FirstPassArgs &a, int line
 }
 
 template <bool COILS>
-FFT_KERNEL void k_first_pass(FirstPassArgs a, int lines_per_wg) {
+__global__ __launch_bounds__(kFftThreads) void k_first_pass(FirstPassArgs a, int lines_per_wg) {
     first_pass_body<COILS>(a, lines_per_wg, blockIdx.x);
 }
 
 // Many problems in one launch: workgroup b runs block blocks[b].y of problem
 // blocks[b].x, whose arguments sit in jobs[blocks[b].x].
 template <bool COILS>
-FFT_KERNEL void k_first_pass_multi(const FirstJob *__restrict__ jobs,
+__global__ __launch_bounds__(kFftThreads) void k_first_pass_multi(const FirstJob *__restrict__ jobs,
                                                              const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const FirstJob &j = jobs[b.x];
@@ -625,12 +617,12 @@ __device__ __forceinline__ void strided_pass_body(const StridedPassArgs &a, int 
 }
 
 template <bool INV, int FORM, bool WIDE = false>
-FFT_KERNEL void k_strided_pass(StridedPassArgs a, int W, int64_t ntc) {
+__global__ __launch_bounds__(kFftThreads) void k_strided_pass(StridedPassArgs a, int W, int64_t ntc) {
     strided_pass_body<INV, FORM, WIDE>(a, W, ntc, xcd_block(blockIdx.x, gridDim.x));
 }
 
 template <bool INV, int FORM, bool WIDE = false>
-FFT_KERNEL void k_strided_pass_multi(const StridedJob *__restrict__ jobs,
+__global__ __launch_bounds__(kFftThreads) void k_strided_pass_multi(const StridedJob *__restrict__ jobs,
                                                                const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const StridedJob &j = jobs[b.x];
@@ -755,12 +747,12 @@ __device__ __forceinline__ void last_pass_body(const LastPassArgs &a, int rows_p
 }
 
 template <bool COILS>
-FFT_KERNEL void k_last_pass(LastPassArgs a, int rows_per_wg, int coils_per_round) {
+__global__ __launch_bounds__(kFftThreads) void k_last_pass(LastPassArgs a, int rows_per_wg, int coils_per_round) {
     last_pass_body<COILS>(a, rows_per_wg, coils_per_round, blockIdx.x);
 }
 
 template <bool COILS>
-FFT_KERNEL void k_last_pass_multi(const LastJob *__restrict__ jobs,
+__global__ __launch_bounds__(kFftThreads) void k_last_pass_multi(const LastJob *__restrict__ jobs,
                                                             const int4 *__restrict__ blocks) {
     const int4 b = blocks[blockIdx.x];
     const LastJob &j = jobs[b.x];
@@ -784,6 +776,7 @@ int threads_for(int elems) {
 }  // namespace
 
 // ------------------------------------------------------------ launchers
+#ifndef NUFFT_FFT_WIDE
 FftLaunch first_pass_launch(const FirstPassArgs &a, int threads) {
     FftLaunch L{64, 0, 0, 1, 0};
     const int64_t total = int64_t(a.B) * a.C * a.rows;
@@ -831,7 +824,7 @@ FftLaunch strided_pass_launch(const StridedPassArgs &a, int threads) {
     return L;
 }
 
-// (the wide instances are made last in this file, after every kernel of the usual sizes)
+// (the wide instances: fft_wide.hip)
 hipError_t launch_wide_strided_pass(const StridedPassArgs &a, const FftLaunch &L, hipStream_t s);
 void launch_wide_strided_pass_multi(const StridedJob *jobs, const int4 *blocks, dim3 grid, dim3 block, bool inverse,
                                     bool split, size_t lds, hipStream_t s);
@@ -928,6 +921,8 @@ hipError_t launch_last_pass_multi(const LastJob *jobs, const int4 *blocks, int64
     return hipGetLastError();
 }
 
+#else  // NUFFT_FFT_WIDE: the instances with 64-bit offsets, in a code object of their own
+
 hipError_t launch_wide_strided_pass(const StridedPassArgs &a, const FftLaunch &L, hipStream_t s) {
     const dim3 grid{unsigned(L.blocks)}, block{unsigned(L.threads)};
     if (!a.inverse)
@@ -951,5 +946,7 @@ void launch_wide_strided_pass_multi(const StridedJob *jobs, const int4 *blocks, 
     else
         launch_kernel((k_strided_pass_multi<true, kPlain, true>), grid, block, lds, s, jobs, blocks);
 }
+
+#endif
 
 }  // namespace nufft
