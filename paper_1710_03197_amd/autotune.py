@@ -36,6 +36,8 @@ TILE_CANDIDATES = {
     3: [(8, 8, 16), (16, 8, 16), (8, 16, 16), (8, 8, 8), (4, 8, 16), (4, 4, 16), (16, 8, 8)],
 }
 CHUNK_CANDIDATES = [256, 512, 1024, 1536, 2048]
+SAMPLE_CANDIDATES = [dict(interp_direct=1), dict(presort=1), dict(presort=2), dict(interp_merge=1),
+                     dict(interp_merge=2), dict(interp_merge=4), dict(weight_table=1), dict(weight_table=-1)]
 FFT_GROUP_CANDIDATES = [256, 512, 1024, 2048, 4096]
 RADIX_CANDIDATES = [1, 2, 3]  # fft_radix schedules besides the default 0
 
@@ -145,9 +147,7 @@ def tune(om: torch.Tensor, N, K=None, J: int = 6, reps: int = 10, path: str | No
     # 2) the gather reading the grid directly instead of staging tiles in LDS,
     #    the gridding's samples pre-permuted into sorted order or read through
     #    the permutation, and runs of sparse tiles per gather item
-    for extra in (dict(interp_direct=1), dict(presort=1), dict(presort=2), dict(interp_merge=1),
-                  dict(interp_merge=2), dict(interp_merge=4), dict(weight_table=1),
-                  dict(weight_table=-1)):
+    for extra in SAMPLE_CANDIDATES:
         opts = dict(best, **extra)
         p = Plan(om, N, K, J, options=opts)
         tried += 1
