@@ -63,7 +63,7 @@ MEASURED_TRAFFIC: dict = {
 def kernels_hash() -> str:
     csrc = os.path.join(ROOT, "paper_1710_03197_amd", "csrc")
     h = hashlib.sha256()
-    for name in sorted(n for n in os.listdir(csrc) if n.endswith(".hip") or n == "device.h"):
+    for name in sorted(n for n in os.listdir(csrc) if n.endswith((".hip", "device.h", "nufft_internal.h"))):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -130,7 +130,9 @@ int nufft_plan(int d, const int64_t *N, const int64_t *K, int J, int64_t M,
  *                 (Section 2.1 "Oversampled FFT"): 0: the fewest passes over
  *                 radices 2 to 6 and 8; 1: radices 4, 8, 2, 3, 5
  *                 taken greedily in that order; 2: 3, 5, 8, 4, 2; 3: 8, 4, 2,
- *                 3, 5, the passes then reversed
+ *                 3, 5, the passes then reversed.  Above K = 64 the first and
+ *                 the last pass are swapped with one of radix 4 or more where
+ *                 there is one
  *   grid_waves    wavefronts per work item of the gridding by 4 x 4 blocks:
  *                 4 (the default, 0 asks for it) sum their partial tiles
  *                 in a fixed order at the end; 1: one wavefront per item,
@@ -194,7 +196,11 @@ int nufft_forward(nufft_plan_t plan, const void *x_dev, void *y_dev, void *strea
 int nufft_adjoint(nufft_plan_t plan, const void *y_dev, void *x_dev, void *stream);
 
 /* B independent transforms sharing the trajectory (Section 2.1, batch mode):
- * x [B][N^d] -> y [B][M] ([B][C][M] in coil mode), and back. */
+ * x [B][N^d] -> y [B][M] ([B][C][M] in coil mode), and back.  Bits: a call
+ * repeated on the same inputs gives the same ones.  Forward results do not
+ * depend on how many transforms share a call; adjoint results may, by float32
+ * rounding: in 2D, calls of five grids (B * C) and more on large problems
+ * are gridded in another summation order than smaller ones. */
 int nufft_forward_batched(nufft_plan_t plan, int B, const void *x_dev, void *y_dev, void *stream);
 int nufft_adjoint_batched(nufft_plan_t plan, int B, const void *y_dev, void *x_dev, void *stream);
 
@@ -282,7 +288,9 @@ int nufft_multi_plan(int P, const nufft_problem_t *probs, void *stream, nufft_mu
  * uploads) and captures the launches into a HIP graph; later calls with the
  * same pointers replay it with one graph launch (the last 4 pointer sets per
  * direction are kept).  Asynchronous on `stream` after the first call; a
- * first call with new pointers must not happen inside a stream capture. */
+ * first call with new pointers must not happen inside a stream capture.  Each
+ * problem's results are bit for bit those of a plan of its own, whatever
+ * shares the launches. */
 int nufft_multi_forward(nufft_multi_t m, const void *const *x_dev, void *const *y_dev, void *stream);
 int nufft_multi_adjoint(nufft_multi_t m, const void *const *y_dev, void *const *x_dev, void *stream);
 

@@ -546,8 +546,8 @@ __global__ __launch_bounds__(256) void k_grid_mfma_multi(const GridArgs *__restr
 }
 
 // V^H on the matrix cores in 2D for several grids (coils, batch entries) that
-// share the trajectory: 16 x 16 tiles, one wavefront per work item and group of
-// kColGrids grids.  The tile is cut into 4 x 4 blocks, and a block is one
+// share the trajectory: 16 x 16 tiles, one or four wavefronts per work item and
+// group of kColGrids grids.  The tile is cut into 4 x 4 blocks, and a block is one
 // product over the samples whose columns are the grids' real and imaginary
 // parts:
 //   H[(x0, x1)][2 g + part] = sum_s (w0_s[x0] w1_s[x1]) v_{s,g,part}

@@ -96,8 +96,10 @@ std::vector<float2> half_phase(int K);
 // Scaling table s(i) = 1 / Phi((i - N/2)/K), i in [0, N) (float32).
 std::vector<float> kb_scaling(int N, int K, int J, double beta);
 // Stockham radix schedule; false if K has a prime factor above 5.  schedule
-// 0: the fewest passes over radices 2..6 and 8, then the smallest sum of radices (the default); 1: 4, 8, 2, 3, 5 taken greedily in
-// that order; 2: 3, 5, 8, 4, 2; 3: 5, 3, 2, 4, 8.
+// 0: the fewest passes over radices 2..6 and 8, then the smallest sum of radices
+// (the default); 1: 4, 8, 2, 3, 5 taken greedily in that order; 2: 3, 5, 8, 4, 2; 3:
+// 5, 3, 2, 4, 8.  Above K = 64 the first and the last pass are swapped with one of
+// radix 4 or more where there is one.
 bool radix_plan(int K, RadixPlan *rp, int schedule = 0);
 // Twiddles of the passes after the first, K - r[0] of them, computed in
 // float64: pass p holds e^{-2 pi i r k / (ns r[p])} as [r = 1 .. r[p]-1][k < ns].
