@@ -49,14 +49,14 @@ TOL = 1e-5
 # otherwise traffic is reported as null.
 MEASURED_TRAFFIC: dict = {
     ("k_grid", "2d_256_golden_radial"): {
-        "kernels_sha": "0ccbae55fe90f5db",
-        "options": {"fft_groups": 512, "grid_chunk": 512, "interp_merge": 2, "tile": [16, 16], "weight_table": 1},
-        "read_bytes": 18482880, "write_bytes": 2308096, "bytes_per_launch": 20790976},
+        "kernels_sha": "021498ab9b3510d6",
+        "options": {"fft_groups": 256, "grid_chunk": 512, "presort": 2, "tile": [16, 16]},
+        "read_bytes": 18485952, "write_bytes": 2308096, "bytes_per_launch": 20794048},
     ("k_grid", "3d_128_koosh"): {
-        "kernels_sha": "0ccbae55fe90f5db",
-        "options": {"fft_groups": 1024, "grid_chunk": 1536, "grid_waves": 1, "interp_merge": 4, "presort": 2,
+        "kernels_sha": "021498ab9b3510d6",
+        "options": {"fft_groups": 2048, "grid_chunk": 1536, "grid_waves": 1, "interp_merge": 2, "presort": 2,
                     "tile": [8, 8, 16], "weight_table": 1},
-        "read_bytes": 798103424, "write_bytes": 149938176, "bytes_per_launch": 948041600},
+        "read_bytes": 798083680, "write_bytes": 149938176, "bytes_per_launch": 948021856},
 }
 
 
