@@ -1328,7 +1328,7 @@ struct nufft_toeplitz_s {
     RadixPlan rp[kMaxDim];
     float2 *tw[kMaxDim] = {nullptr, nullptr, nullptr};
     float *ones[kMaxDim] = {nullptr, nullptr, nullptr};
-    float *inv[kMaxDim] = {nullptr, nullptr, nullptr};  // 1 / (2 N_a)
+    float *inv[kMaxDim] = {nullptr, nullptr, nullptr};  // 1 / prod(2N) on the last axis, 1 on the others
     float2 *phat = nullptr;   // [prod(2N)]
     int cap = 0;              // grids the workspace holds
     float2 *grid = nullptr;   // pass buffers, [cap][prod(2N)] each
@@ -1374,7 +1374,7 @@ int ensure_toeplitz_workspace(nufft_toeplitz_s *t, int grids) {
     return NUFFT_OK;
 }
 
-// psf = true: image = grid = 2N, scale 1/(2N_a) (the point-spread function's
+// psf = true: image = grid = 2N, scale 1/prod(2N) (the point-spread function's
 // transform); false: image N on grid 2N, no scaling (the application).
 FftGeom toeplitz_fft(const nufft_toeplitz_s *t, bool psf) {
     FftGeom f;
@@ -2024,9 +2024,13 @@ int nufft_toeplitz_plan(nufft_plan_t plan, const float *w_dev, void *stream, nuf
         t->N[a] = plan->N[a];
         t->P[a] = N2[a];
         t->elems *= N2[a];
+    }
+    for (int a = 0; a < d; ++a) {
         if (!radix_plan(int(N2[a]), &t->rp[a])) return fail(NUFFT_ERR_UNSUPPORTED, "no radix plan for 2N");
         std::vector<float> ones(size_t(plan->N[a]), 1.0f);
-        std::vector<float> inv(size_t(N2[a]), float(1.0 / double(N2[a])));
+        // the whole factor on one axis: one rounding.  (1 / 2N_a on each axis put the
+        // operator of a 120 x 120 x 96 image 1.6e-7 too high, as much as all else it rounds.)
+        std::vector<float> inv(size_t(N2[a]), a == d - 1 ? float(1.0 / double(t->elems)) : 1.0f);
         hipError_t e;
         if ((e = upload(&t->tw[a], pass_twiddles(int(N2[a]), t->rp[a]))) != hipSuccess ||
             (e = upload(&t->ones[a], ones)) != hipSuccess || (e = upload(&t->inv[a], inv)) != hipSuccess) {
@@ -2078,7 +2082,7 @@ int nufft_toeplitz_plan(nufft_plan_t plan, const float *w_dev, void *stream, nuf
     if (!st) {
         // P = F(p placed at Delta mod 2N) / prod(2N): the forward passes with
         // image = grid = 2N place the centred p circularly; the scale tables
-        // carry 1 / (2N_a)
+        // carry 1 / prod(2N)
         FftGeom f = toeplitz_fft(t.get(), true);
         f.coils = nullptr;
         f.C = 1;

@@ -151,7 +151,12 @@ hipError_t launch_strided_pass_multi(const StridedJob *jobs, const int4 *, int64
     note("strided_multi K=%d inverse=%d wide=%d", jobs[0].a.K, inverse, wide);
     return hipSuccess;
 }
-hipError_t launch_first_pass(const FirstPassArgs &, hipStream_t) { return hipSuccess; }
+hipError_t launch_first_pass(const FirstPassArgs &a, hipStream_t) {
+    float s = 1.0f;  // the first pixel's scale, multiplied as the kernel does
+    for (int ax = a.d - 2; ax >= 0; --ax) s *= a.scale[ax][0];
+    note("first K=%d scale=%a", a.K, a.scale[a.d - 1][0] * s);
+    return hipSuccess;
+}
 hipError_t launch_last_pass(const LastPassArgs &, hipStream_t) { return hipSuccess; }
 hipError_t launch_first_pass_multi(const FirstJob *, const int4 *, int64_t, int, bool, size_t, hipStream_t) {
     return hipSuccess;

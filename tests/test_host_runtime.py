@@ -335,3 +335,15 @@ def test_toeplitz_operator_is_made_with_room_for_the_coils(host, failures):
     assert (host.lib.stub_live_bytes() == before) == (failures == 0)
     host.call("nufft_toeplitz_destroy", t)
     host.call("nufft_destroy", p)
+
+
+@pytest.mark.parametrize("N", [(120, 120, 96), (80, 72, 60), (30, 50, 18), (100, 60), (162, 90), (54,)])
+def test_toeplitz_spectrum_is_scaled_by_one_rounding(host, N):
+    """1 / prod(2N) reaches the spectrum to half a unit in the last place."""
+    p, _ = host.plan(N, tuple(2 * n for n in N), 6, np.full((10, len(N)), 0.5, np.float32))
+    t = ctypes.c_void_p()
+    log = host.call("nufft_toeplitz_plan", p, None, None, ctypes.byref(t))
+    scale = float.fromhex([e["scale"] for e in log if e["what"] == "first"][-1])
+    assert abs(scale * np.prod([2.0 * n for n in N]) - 1.0) <= 2.0 ** -24
+    host.call("nufft_toeplitz_destroy", t)
+    host.call("nufft_destroy", p)
